@@ -20,7 +20,10 @@
  *               batched DFT_a (Fig. 9, Section 3.2);
  *   AUTO        a per-shape choice: the autotuner's measured choice when
  *               one is recorded, otherwise SLAB below 256 MiB (arrays the
- *               Infinity Cache can hold) and PENCIL from 256 MiB on.
+ *               Infinity Cache can hold) and PENCIL from 256 MiB on; with
+ *               lengths that are not powers of two PENCIL, or SLAB from 2^20
+ *               points to 2.5 GiB where the pencil passes' rows would not
+ *               start on 128-byte lines.
  *
  * Data: complex64 = two IEEE binary32 (re, im), interleaved, 8 bytes per
  * point; C order (n0, n1, n2), n2 contiguous; device pointers, 16-byte
@@ -214,8 +217,10 @@ enum dft3d_option {
                                 storing rows one row length apart; -1
                                 (default) = 2 for split precision and for
                                 arrays with an axis of 2048, else 0 (the
-                                faster order measured for each).  Other
-                                values: INVALID_ARG */
+                                faster order measured for each).  Arrays
+                                with other lengths keep the rotation, and
+                                with -1 run the cycle from 2.5 GiB up.
+                                Other values: INVALID_ARG */
   DFT3D_OPT_NUM_PASSES = 100 /* read-only: number of kernel launches */
 };
 
@@ -231,10 +236,12 @@ const char* dft3d_status_string(int status);
  * [1, 4096].  Powers of two run on every schedule.  Other lengths (the
  * paper's experiments use powers of two; it leaves sizes its process grid
  * does not divide to future work, Section 3.2) run with FP32 precision and
- * the natural layout on every schedule (AUTO picks pencil), one pass per
+ * the natural layout on every schedule, one pass per
  * such axis (rotate-on-write in the pencil schedule, in layout in the slab
- * and volumetric schedules): a mixed-radix pass (radices 2, 3, 4, 5, 7, 8,
- * 10, 11, 13, 16) when every prime factor of n_d is at most 13, else for
+ * and volumetric schedules): a mixed-radix pass when every prime factor of
+ * n_d is at most 13 (in two register steps where n_d <= 1024 splits into two
+ * factors of at most 40, else in stages of radix 2, 3, 4, 5, 7, 8, 10, 11,
+ * 13, 16), else for
  * the primes n_d whose n_d - 1 has that property and that a Rader kernel is
  * compiled for a Rader pass (a circular convolution of length n_d - 1 done
  * with two mixed-radix FFTs, see DFT3D_OPT_RADER), else a Bluestein pass (the DFT of length n as a circular

@@ -5,6 +5,7 @@
 #include <map>
 #include <new>
 #include <string>
+#include <tuple>
 
 #include "../../include/dft3d.h"
 #include "internal.h"
@@ -57,6 +58,14 @@ void free_workspace(dft3d_plan_s* p) {
   p->ws_owned = false;
 }
 
+// The twiddle table of a mixed-radix or Rader pass: (length, A, radix code).
+using MixedKey = std::tuple<int64_t, int, uint64_t>;
+MixedKey mixed_key(const Pass& ps) {
+  if (ps.k->rader) return {ps.rader_n - 1, 0, (uint64_t)ps.args.twp_mask};
+  if (ps.k->two_step) return {ps.args.res_mask, ps.args.res_shift, 0};
+  return {ps.args.res_mask, 0, (uint64_t)ps.args.twp_mask};
+}
+
 // (Re)build the pass list and upload one root table per distinct length.
 int rebuild(dft3d_plan_s* p) {
   std::vector<Pass> passes;
@@ -81,8 +90,9 @@ int rebuild(dft3d_plan_s* p) {
   // the filter stored right after the chirp)
   std::map<int64_t, int64_t> offsets;
   std::map<std::pair<int, int64_t>, int64_t> bl_offsets;
-  // mixed-radix stage twiddles per length n and radix code (value: offset)
-  std::map<std::pair<int64_t, uint64_t>, int64_t> mx_offsets;
+  // mixed-radix twiddles (value: offset): staged passes per length n and
+  // radix code (n, 0, code), two-step passes per length and split (n, A, 0)
+  std::map<MixedKey, int64_t> mx_offsets;
   // Rader tables per prime length n (value: offset)
   std::map<int64_t, int64_t> rd_offsets;
   int64_t total = 0;
@@ -98,10 +108,10 @@ int rebuild(dft3d_plan_s* p) {
   for (const Pass* pp : all) {
     const Pass& ps = *pp;
     if (ps.k->rader) {  // stage twiddles of n - 1, and the Rader tables of n
-      const std::pair<int64_t, uint64_t> key{ps.rader_n - 1, (uint64_t)ps.args.twp_mask};
+      const MixedKey key = mixed_key(ps);
       if (!mx_offsets.count(key)) {
         mx_offsets[key] = total;
-        total += key.first;
+        total += std::get<0>(key);
       }
       if (!rd_offsets.count(ps.rader_n)) {
         rd_offsets[ps.rader_n] = total;
@@ -110,10 +120,10 @@ int rebuild(dft3d_plan_s* p) {
       continue;
     }
     if (ps.k->mixed) {
-      const std::pair<int64_t, uint64_t> key{ps.args.res_mask, (uint64_t)ps.args.twp_mask};
+      const MixedKey key = mixed_key(ps);
       if (!mx_offsets.count(key)) {
         mx_offsets[key] = total;
-        total += key.first;
+        total += std::get<0>(key);
       }
       continue;
     }
@@ -141,8 +151,13 @@ int rebuild(dft3d_plan_s* p) {
     else
       make_leaf_table((int)-kv.first, reinterpret_cast<unsigned short*>(host.data() + kv.second));
   }
-  for (auto& kv : mx_offsets)
-    make_mixed_twiddles(kv.first.first, kv.first.second, host.data() + kv.second);
+  for (auto& kv : mx_offsets) {
+    const int64_t len = std::get<0>(kv.first);
+    if (const int a = std::get<1>(kv.first))
+      make_two_step_twiddles(len, a, host.data() + kv.second);
+    else
+      make_mixed_twiddles(len, std::get<2>(kv.first), host.data() + kv.second);
+  }
   for (auto& kv : rd_offsets) make_rader_tables(kv.first, host.data() + kv.second);
   for (auto& kv : bl_offsets) {
     if (kv.first.first == 1)
@@ -173,12 +188,12 @@ int rebuild(dft3d_plan_s* p) {
     twp.clear();
     for (const Pass& ps : list) {
       if (ps.k->rader) {
-        tw.push_back(mx_offsets[{ps.rader_n - 1, (uint64_t)ps.args.twp_mask}]);
+        tw.push_back(mx_offsets[mixed_key(ps)]);
         twp.push_back(rd_offsets[ps.rader_n]);
         continue;
       }
       if (ps.k->mixed) {  // the stage twiddles of the length
-        tw.push_back(mx_offsets[{ps.args.res_mask, (uint64_t)ps.args.twp_mask}]);
+        tw.push_back(mx_offsets[mixed_key(ps)]);
         twp.push_back(0);
         continue;
       }

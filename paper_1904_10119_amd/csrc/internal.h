@@ -66,6 +66,8 @@ struct KernelInfo {
   int mfma_leaf = 0;  // split-precision MFMA passes: the leaf length (16 or 32)
   int rader = 0;      // > 0: Rader pass for prime lengths up to n - 1 (variant as mixed)
   int mfma_wide = 0;  // 1: MFMA one-tile pass with twice the default tile
+  int two_step = 0;   // > 0: mixed-radix pass in two register steps (two_step_kernel.h);
+                      // the first step of a compiled length, 1 for any length
   int halves = 0;     // 1: rotate-on-write pass of length n as two half-length
                       // transforms after a radix-2 split (halves_kernel.h)
 };
@@ -102,6 +104,23 @@ int mixed_variant(uint64_t code);
 // kernel's radices (2, 3, 4, 5, 7, 8, 10, 11, 13, 16) whose product is at
 // most 2048 and that a compiled mixed-radix kernel runs at that length.
 bool radix_code_valid(uint64_t code);
+// The first step A of the split n = A B (A <= B <= 40, the most even one:
+// fewest registers) of a two-step pass (two_step_kernel.h); 0 for lengths
+// below 6 or above 1024, with a prime factor above 13, or without a split.
+constexpr int two_step_split(int64_t n) {
+  if (n < 6 || n > 1024) return 0;
+  int64_t m = n;
+  for (int f = 2; f <= 13; ++f)
+    while (m % f == 0) m /= f;
+  if (m != 1) return 0;
+  for (int a = 32; a >= 2; --a)
+    if (n % a == 0 && (int64_t)a * a <= n) return n / a <= 40 ? a : 0;
+  return 0;
+}
+// The two-step kernel for length n and the load and store modes, or null.
+const KernelInfo* find_two_step_kernel(int64_t n, int lmode, int smode);
+// Twiddles of a two-step pass: out[tm (n / a) + j] = w_n^{tm j}, from FP64.
+void make_two_step_twiddles(int64_t n, int a, float2* out);
 // The product of a radix code's stages.
 int64_t radix_code_length(uint64_t code);
 // Whether a length is supported: every length 1..4096 (powers of two,

@@ -315,9 +315,13 @@ struct Builder {
   // (mixed_kernel.h documents the argument fields).
   void add_mixed(int64_t n, const Field* f, int nf, int64_t ijs, int64_t oks,
                  const std::string& label, int lmode = MODE_ROW, int smode = MODE_COL) {
-    const uint64_t code =
-        opt.radices && radix_code_length(opt.radices) == n ? opt.radices : mixed_radix_code(n);
-    const KernelInfo* k = find_mixed_kernel(n, code, opt.tile, lmode, smode);
+    const bool asked = opt.radices && radix_code_length(opt.radices) == n;
+    const uint64_t code = asked ? opt.radices : mixed_radix_code(n);
+    // two register steps where the length splits into them, the staged
+    // kernel for other lengths, an asked-for tile or radix sequence
+    const KernelInfo* k = nullptr;
+    if (!asked && opt.tile <= 0) k = find_two_step_kernel(n, lmode, smode);
+    if (!k) k = find_mixed_kernel(n, code, opt.tile, lmode, smode);
     if (!k || !code) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;
       return;
@@ -329,6 +333,7 @@ struct Builder {
     p.args.oks = oks;
     p.args.res_mask = n;
     p.args.twp_mask = (int64_t)code;
+    p.args.res_shift = k->two_step;
     p.args.xcd_remap = opt.xcd_remap;
     p.tw_len = n;
     p.label = label;
@@ -668,6 +673,57 @@ void axis_pass(Builder& b, int64_t n, int lmode, int smode, const Field* f, int 
   }
 }
 
+// The cycle (A, B, C) -> (B, C, A) -> (C, A, B) -> (A, B, C) of
+// pencil_swapped for shapes with lengths other than powers of two (general
+// pencil index; powers of two among the axes run the mixed-radix pass).
+// Taken from 2.5 GiB up, measured against the rotation: 1000^3 11.5 -> 10.1
+// ms, 1001^3 14.1 -> 11.2, 945^3 9.98 -> 8.85, 810^3 5.97 -> 5.59, 700^3
+// 3.80 -> 3.57; below it the rotation is the faster one: 675^3 3.06 against
+// 3.31 ms, 600^3 2.06 / 2.32, 1000 x 1000 x 300 2.82 / 3.05.  The rotation
+// stores rows a whole plane apart, the cycle one row length apart.
+constexpr int64_t kCycleBytes = int64_t(5) << 29;
+void pencil_cycled_other(Builder& b, const int64_t n[3]) {
+  const int64_t A = n[0], B = n[1], C = n[2];
+  const struct {
+    int axis;
+    int64_t len, c0, in0, c1, out1, row;
+  } steps[3] = {{2, C, A, B * C, B, C * A, A},
+                {0, A, B, C * A, C, A * B, B},
+                {1, B, C, A * B, A, B * C, C}};
+  for (const auto& s : steps) {
+    if (b.status != DFT3D_OK) return;
+    Field f[2] = {{s.c0, s.in0, 1}, {s.c1, s.len, s.out1}};
+    char lab[64];
+    std::snprintf(lab, sizeof lab, "pencil%d DFT%lld x%lld cyc", s.axis, (long long)s.len,
+                  (long long)(s.c0 * s.c1));
+    axis_pass(b, s.len, MODE_ROW, MODE_COL, f, 2, 1, s.row, lab);
+  }
+}
+
+// Untuned AUTO over lengths other than powers of two: the slab schedule,
+// whose passes keep the layout, where every axis has a two-step (or
+// power-of-two) pass and the pencil rotation would write rows that do not
+// start on 128-byte lines (the product of the other two axes is no multiple
+// of 16 points): neighbouring tiles then write parts of the same lines, and
+// with two or more workgroups a CU (lengths up to 640) they leave the L2
+// half-written.  Measured, rotation / slab: 375 x 486 x 400 737 / 673 us,
+// 375^3 659 / 538, 455 x 325 x 195 339 / 270, 525^3 1878 / 1484, 105^3 22.5
+// / 20.9; longer misaligned passes 675^3 3.06 / 3.24 ms; aligned ones 324^3
+// 326 / 341 us, 600 x 600 x 18 64 / 72.  Below 2^20 points both are bound by
+// launches.
+bool slab_suits_other(const int64_t n[3], const Options& opt) {
+  const int64_t total = n[0] * n[1] * n[2];
+  if (total < (int64_t(1) << 20) || total * 8 >= kCycleBytes || opt.tile > 0 || opt.radices ||
+      opt.pencil_order >= 0 || opt.pencil_group)
+    return false;
+  bool misaligned = false;
+  for (int d = 0; d < 3; ++d) {
+    if (!two_step_split(n[d])) return false;
+    misaligned = misaligned || (n[d] <= 640 && total / n[d] % 16 != 0);
+  }
+  return misaligned;
+}
+
 // Grouped pencil schedule: planes of axis 0 taken G at a time through the
 // first two passes, so that a group's intermediate (G n1 n2 points, about
 // 256 MB) is read back by the second pass while it is still in the
@@ -817,9 +873,10 @@ int build_passes(const int64_t n[3], int schedule, int layout, const Options& gi
   Builder b{opt, passes, total};
   resolved = schedule;
   if (schedule == DFT3D_SCHED_AUTO)
-    resolved = shuffled ? DFT3D_SCHED_VOLUMETRIC
-                        : ((total * 8 < kStreamBytes && !any_other) ? DFT3D_SCHED_SLAB
-                                                                    : DFT3D_SCHED_PENCIL);
+    resolved = shuffled    ? DFT3D_SCHED_VOLUMETRIC
+               : any_other ? (slab_suits_other(n, opt) ? DFT3D_SCHED_SLAB : DFT3D_SCHED_PENCIL)
+               : total * 8 < kStreamBytes ? DFT3D_SCHED_SLAB
+                                          : DFT3D_SCHED_PENCIL;
   // Untuned AUTO splits only 4096-long axes (a 4096 pencil leaves tiles of
   // four pencils); measured at 2048x1024x512, the 2048 pass beats its split.
   const int64_t split_max =
@@ -837,6 +894,11 @@ int build_passes(const int64_t n[3], int schedule, int layout, const Options& gi
              is_pow2(n[1]) && is_pow2(n[2]) && n[0] <= split_max && n[1] <= split_max &&
              n[2] <= split_max) {
     pencil_swapped(b, n);
+    assign_chain(passes, 0, need_ws);
+  } else if (resolved == DFT3D_SCHED_PENCIL && any_other && opt.pencil_order < 0 &&
+             total * 8 >= kCycleBytes && n[0] <= split_max && n[1] <= split_max &&
+             n[2] <= split_max) {
+    pencil_cycled_other(b, n);
     assign_chain(passes, 0, need_ws);
   } else if (resolved == DFT3D_SCHED_PENCIL) {
     int64_t cur[3] = {n[0], n[1], n[2]};
@@ -1081,6 +1143,9 @@ void describe_list(std::ostringstream& os, const std::vector<Pass>& passes) {
         os << (first ? "" : ",") << p.k->mfma_leaf;
       if (n > 1) os << "," << n;
     }
+    os << "],\"split\":[";
+    if (p.k->two_step)  // two-step passes: the register DFTs the radices are grouped into
+      os << p.args.res_shift << "," << p.args.res_mask / p.args.res_shift;
     os << "]"
        << ",\"mfma_leaf\":" << p.k->mfma_leaf << ",\"threads\":" << p.k->threads
        << ",\"lds_bytes\":" << p.k->lds_bytes << ",\"pencils\":" << p.args.B

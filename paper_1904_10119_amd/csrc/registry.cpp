@@ -24,6 +24,12 @@ void register_kernels_mixed_fixed(std::vector<KernelInfo>& v);
 void register_kernels_rader(std::vector<KernelInfo>& v);
 void register_kernels_rader_fixed(std::vector<KernelInfo>& v);
 void register_kernels_halves(std::vector<KernelInfo>& v);
+void register_kernels_two_step_a(std::vector<KernelInfo>& v);
+void register_kernels_two_step_b(std::vector<KernelInfo>& v);
+void register_kernels_two_step_c(std::vector<KernelInfo>& v);
+void register_kernels_two_step_d(std::vector<KernelInfo>& v);
+void register_kernels_two_step_e(std::vector<KernelInfo>& v);
+void register_kernels_two_step_f(std::vector<KernelInfo>& v);
 
 const std::vector<KernelInfo>& kernel_registry() {
   static const std::vector<KernelInfo> table = [] {
@@ -46,6 +52,12 @@ const std::vector<KernelInfo>& kernel_registry() {
     register_kernels_rader(v);
     register_kernels_rader_fixed(v);
     register_kernels_halves(v);
+    register_kernels_two_step_a(v);
+    register_kernels_two_step_b(v);
+    register_kernels_two_step_c(v);
+    register_kernels_two_step_d(v);
+    register_kernels_two_step_e(v);
+    register_kernels_two_step_f(v);
     return v;
   }();
   return table;
@@ -110,16 +122,22 @@ const KernelInfo* find_mixed_kernel(int64_t n, uint64_t code, int tile, int lmod
   const KernelInfo* best = nullptr;
   if (tile <= 0)  // a kernel compiled for this length, code and modes, if any
     for (const KernelInfo& k : kernel_registry())
-      if (k.mixed && k.fixed_n == n && k.fixed_code == code && k.lmode == lmode &&
+      if (k.mixed && !k.two_step && k.fixed_n == n && k.fixed_code == code && k.lmode == lmode &&
           k.smode == smode)
         return &k;
   for (const KernelInfo& k : kernel_registry())
-    if (k.mixed == variant && k.fixed_n == 0 && k.n > n && k.lmode == lmode &&
+    if (k.mixed == variant && !k.two_step && k.fixed_n == 0 && k.n > n && k.lmode == lmode &&
         k.smode == smode && mixed_kernel_runs(k.mixed, k.n, code)) {
       if (tile > 0 && k.tile == tile) return &k;  // the asked-for tile, if any
       if (!best || k.n < best->n) best = &k;      // else the first, smallest
     }
   return best;
+}
+
+const KernelInfo* find_two_step_kernel(int64_t n, int lmode, int smode) {
+  for (const KernelInfo& k : kernel_registry())
+    if (k.two_step && k.fixed_n == n && k.lmode == lmode && k.smode == smode) return &k;
+  return nullptr;
 }
 
 uint64_t mixed_radix_code(int64_t n) {

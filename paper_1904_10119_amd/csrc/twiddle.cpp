@@ -247,4 +247,14 @@ void make_mixed_twiddles(int64_t n, uint64_t code, float2* out) {
   if (ns != n) return;  // the code always multiplies to n (mixed_radix_code)
 }
 
+void make_two_step_twiddles(int64_t n, int a, float2* out) {
+  const int64_t b = n / a;
+  for (int64_t tm = 0; tm < a; ++tm)
+    for (int64_t j = 0; j < b; ++j) {
+      double c, s;
+      root_fp64(tm * j, n, c, s);
+      out[tm * b + j] = make_float2((float)c, (float)(-s));
+    }
+}
+
 }  // namespace dft3d

@@ -1,0 +1,217 @@
+// Mixed-radix passes in two register steps: a length n = A B with A <= B,
+// both free of prime factors above 13, is transformed with one exchange
+// through LDS (the four-step identity of eq. (3) with the whole inner DFTs
+// in registers).
+//
+// Step 1: butterfly t (t < B) of a pencil reads its points t + r B (r < A)
+// straight from global memory, transforms them with DFT_A and leaves output
+// r at row r, column t of the pencil's A x B table in LDS.  Step 2:
+// butterfly tm (tm < A) reads row tm, multiplies entry j by w_n^{tm j},
+// transforms with DFT_B and stores output j as point k = tm + A j straight
+// to global memory.  Against the staged pass (mixed_kernel.h: an LDS round
+// trip and two barriers a radix) every point crosses LDS once and each
+// thread has its A loads in flight together.
+//
+// The butterflies of a tile of T pencils are numbered through, one of step 1
+// and at most one of step 2 a thread.  ROW orders run lanes along the pencil (t, tm
+// fastest), COL orders across the pencils.  LDS rows have an odd pitch and
+// pencils an odd stride in 8-byte units, so neither order has bank
+// conflicts beyond the 2-way split of a 64-lane 8-byte access.
+//
+// What bounds it: memory from about 10^7 points up (57 VALU instructions a
+// point at n = 375, half of what the card issues at the copy rate), launch and
+// load latency below.  The tile is 16 pencils so that a COL row segment is
+// one 128-byte line: 400^3 takes 603 us so, 762 us in tiles of 8 pencils
+// (64-byte segments) and 629 us in tiles of 32 (fewer workgroups a CU).
+// Against the staged pass (same orders, MI355X): 96^3 25.0 -> 17.9 us, 90^3
+// 30.4 -> 18.7, 150^3 62.9 -> 32.6, 252^3 209 -> 141 (5.4 TB/s a pass),
+// 324^3 462 -> 326, 540^3 2370 -> 1481, 900^3 10.3 -> 8.6 ms, 640^3 2.95 ->
+// 2.75 ms; no faster at 1000^3 in the rotation's order (11.4 / 11.5 ms; 10.1
+// in the cycle, against 10.3).  A kernel for any length with a radix switch
+// took 177 us at 250^3 where the compiled lengths take 142: it holds the
+// registers of the largest radix (120 against 93).
+//
+// PassArgs fields used: pencil fields and element strides as for every
+// pass, res_mask = n, twp_mask = the length's radix code (as the staged
+// pass), res_shift = A.  Table: tw[tm B + j] = w_n^{tm j}, from FP64.
+#pragma once
+
+#include "mixed_kernel.h"
+
+namespace dft3d {
+
+__host__ __device__ constexpr int two_step_pitch(int b) { return b | 1; }
+__host__ __device__ constexpr int two_step_stride(int a, int b) {
+  return (a * two_step_pitch(b)) | 1;
+}
+
+// id = quot d + rem for 0 <= id < 1600 and 1 <= d <= 40 by a multiplication
+// with m = ceil(65536 / d) (exact while id (m d - 65536) < 65536).
+__device__ __forceinline__ void split_id(int id, int d, int m, int& quot, int& rem) {
+  quot = (id * m) >> 16;
+  rem = id - quot * d;
+}
+constexpr int kTwoStepMaxIds = 1600;
+
+// Step 1 of radix R over the tile: B butterflies a pencil.
+template <int R, int T, int LM>
+__device__ __forceinline__ void two_step_first(const float2* src, const PassArgs& a,
+                                               int64_t tile, float2* lds, int B, int tid,
+                                               int th) {
+  const int pitch = two_step_pitch(B), sq = two_step_stride(R, B);
+  const int mb = (65535 + B) / B;
+  for (int id = tid; id < T * B; id += th) {
+    int q, t;
+    if constexpr (LM == MODE_ROW) {
+      split_id(id, B, mb, q, t);
+    } else {
+      q = id % T;
+      t = id / T;
+    }
+    // pencils past the end of a ragged last tile read the last pencil
+    int64_t b = tile * T + q;
+    b = b < a.B ? b : a.B - 1;
+    const float2* s =
+        src + pencil_offset_any(b, a.m0, a.m1, a.s0, a.s1, a.is0, a.is1, a.is2);
+    float2 v[R];
+    if constexpr (LM == MODE_ROW) {
+      s += t;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = s[r * B];
+    } else {
+      s += t * a.ijs;
+      const int64_t step = B * a.ijs;
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = s[r * step];
+    }
+    if (a.conj_in) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r].y = -v[r].y;
+    }
+    dft_mixed<R>(v);
+    float2* w = lds + q * sq + t;
+#pragma unroll
+    for (int r = 0; r < R; ++r) w[r * pitch] = v[r];
+  }
+}
+
+// Step 2 of radix R over the tile (A butterflies a pencil) and the store.
+// The first butterfly's twiddles are read before the barrier that ends
+// step 1 where they fit in registers beside its data.
+template <int R, int T, int SM>
+__device__ __forceinline__ void two_step_second(float2* dst, const float2* __restrict__ tw,
+                                                const PassArgs& a, int64_t tile,
+                                                const float2* lds, int A, int tid, int th) {
+  constexpr bool EARLY = R <= 16;
+  const int pitch = two_step_pitch(R), sq = two_step_stride(A, R);
+  const int ma = (65535 + A) / A;
+  auto place = [&](int id, int& q, int& tm) {
+    if constexpr (SM == MODE_ROW) {
+      split_id(id, A, ma, q, tm);
+    } else {
+      q = id % T;
+      tm = id / T;
+    }
+  };
+  int q, tm;
+  place(tid, q, tm);
+  float2 w[R];
+  if constexpr (EARLY) {
+    if (tid < T * A) {
+#pragma unroll
+      for (int j = 1; j < R; ++j) w[j] = tw[tm * R + j];
+    }
+  }
+  __syncthreads();  // every output of step 1 is in LDS
+  for (int id = tid; id < T * A; id += th) {
+    if (id != tid || !EARLY) {
+      place(id, q, tm);
+#pragma unroll
+      for (int j = 1; j < R; ++j) w[j] = tw[tm * R + j];
+    }
+    const float2* row = lds + q * sq + tm * pitch;
+    float2 v[R];
+    v[0] = row[0];
+#pragma unroll
+    for (int j = 1; j < R; ++j) v[j] = cmul(row[j], w[j]);
+    dft_mixed<R>(v);
+    if (a.conj_out) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) v[j].y = -v[j].y;
+    }
+    const int64_t b = tile * T + q;
+    if (b < a.B) {
+      float2* d = dst + pencil_offset_any(b, a.m0, a.m1, a.s0, a.s1, a.os0, a.os1, a.os2);
+      if constexpr (SM == MODE_ROW) {
+        d += tm;
+#pragma unroll
+        for (int j = 0; j < R; ++j) d[j * A] = v[j];
+      } else {
+        d += tm * a.oks;
+        const int64_t step = A * a.oks;
+#pragma unroll
+        for (int j = 0; j < R; ++j) d[j * step] = v[j];
+      }
+    }
+  }
+}
+
+// One workgroup per tile of T pencils; the length A * B, the tile and the
+// orders are compile-time constants (sizes and LDS offsets fold, no radix
+// switch, and each length has its own register count).
+template <int A, int B, int T, int TH, int LM, int SM>
+__global__ void __launch_bounds__(TH)
+fft_two_step_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
+                   const float2* __restrict__ twp, const PassArgs a) {
+  __shared__ float2 lds[T * two_step_stride(A, B)];
+  const int tid = threadIdx.x;
+  const int64_t tile = tile_index(blockIdx.x, gridDim.x, a.xcd_remap);
+  two_step_first<A, T, LM>(src, a, tile, lds, B, tid, TH);
+  two_step_second<B, T, SM>(dst, tw, a, tile, lds, A, tid, TH);
+}
+
+// Threads of a two-step workgroup: a butterfly of step 1 for each (at most
+// 40 x 16 or 8 x 64).
+constexpr int two_step_threads(int b, int t) { return (t * b + 63) / 64 * 64; }
+
+template <int A, int B, int T, int LM, int SM>
+hipError_t launch_two_step(const PassArgs& a, const float2* src, float2* dst, const float2* tw,
+                           const float2* twp, hipStream_t stream) {
+  const int64_t blocks = (a.B + T - 1) / T;
+  if (blocks <= 0) return hipSuccess;
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+  if (a.res_shift != A || a.res_mask != A * B) return hipErrorInvalidValue;
+  constexpr int TH = two_step_threads(B, T);
+  hipLaunchKernelGGL((fft_two_step_kernel<A, B, T, TH, LM, SM>), dim3((unsigned)blocks),
+                     dim3(TH), 0, stream, src, dst, tw, twp, a);
+  return hipGetLastError();
+}
+
+template <int A, int B, int T, int LM, int SM>
+KernelInfo kernel_info_two_step() {
+  constexpr int LDS = T * two_step_stride(A, B) * 8, TH = two_step_threads(B, T);
+  static_assert(LDS <= 160 * 1024 && T * B <= kTwoStepMaxIds && TH <= 1024, "tile fits");
+  // n: a length bound above the kernel's length, as for the staged kernels
+  KernelInfo k{A * B + 1, T, LM, SM, 0, TH, LDS, &launch_two_step<A, B, T, LM, SM>, 0, 0};
+  k.mixed = mixed_variant(mixed_radix_code(A * B));
+  k.two_step = A;
+  k.fixed_n = A * B;
+  return k;
+}
+
+// The kernels of the lengths LO <= n < HI that split, in tiles of 16 pencils
+// (128-byte row segments) for every order.
+template <int LO, int HI>
+void add_two_step_kernels(std::vector<KernelInfo>& v) {
+  if constexpr (HI - LO > 1) {
+    add_two_step_kernels<LO, (LO + HI) / 2>(v);
+    add_two_step_kernels<(LO + HI) / 2, HI>(v);
+  } else if constexpr (two_step_split(LO) > 0) {
+    constexpr int A = two_step_split(LO), B = LO / A;
+    v.push_back(kernel_info_two_step<A, B, 16, MODE_ROW, MODE_COL>());
+    v.push_back(kernel_info_two_step<A, B, 16, MODE_ROW, MODE_ROW>());
+    v.push_back(kernel_info_two_step<A, B, 16, MODE_COL, MODE_COL>());
+  }
+}
+
+}  // namespace dft3d

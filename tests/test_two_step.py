@@ -1,0 +1,157 @@
+"""Two-step mixed-radix passes (a length n = A B in two register DFTs and one
+exchange): the split and its formulas on the CPU, the pass lists that use
+them, and GPU parity against the oracle at the edges of the kernels' range.
+
+Tolerance on the GPU: log2(n) + 1 rounding levels per axis at the tol(N) rate
+of 1e-6 / 18 per level, the bar of every mixed-radix axis."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1904_10119_amd import dft3d, inputs
+
+TWO_STEP = {6: [2, 3], 30: [5, 6], 96: [8, 12], 125: [5, 25], 143: [11, 13], 375: [15, 25],
+            486: [18, 27], 720: [24, 30], 1000: [25, 40], 1008: [28, 36], 1024: [32, 32]}
+
+
+def smooth13(n):
+    for f in (2, 3, 5, 7, 11, 13):
+        while n % f == 0:
+            n //= f
+    return n == 1
+
+
+def first_pass(n, **kw):
+    return dft3d.describe((3, 5, n), "pencil", **kw)["passes"][0]
+
+
+def test_which_lengths_split():
+    """Smooth lengths 6..1024 with a factor pair A <= B <= 40 take a two-step
+    pass with the most even pair; a tile option keeps the staged kernels."""
+    for n in range(2, 1101):
+        if n & (n - 1) == 0 or not smooth13(n):
+            continue
+        p = first_pass(n)
+        pairs = [a for a in range(2, 33) if n % a == 0 and a * a <= n and n // a <= 40]
+        assert p["split"] == ([max(pairs), n // max(pairs)] if pairs and 6 <= n <= 1024 else []), n
+        if p["split"]:
+            assert p["fixed_n"] == n and p["tile"] == 16
+            assert p["threads"] >= 16 * p["split"][1] and p["lds_bytes"] <= 160 * 1024
+        assert first_pass(n, tile=16)["split"] == []
+
+
+@pytest.mark.parametrize("n", sorted(TWO_STEP))
+def test_two_step_formulas(n):
+    """Step 1: DFT_A of x[t + r B] over r; step 2: DFT_B over t of row tm
+    times w_n^{tm t}, output j at tm + A j -- equals the direct sum."""
+    p = first_pass(n)
+    if n & (n - 1):
+        assert p["split"] == TWO_STEP[n]
+    A, B = TWO_STEP[n]
+    g = np.random.default_rng(n)
+    x = g.standard_normal(n) + 1j * g.standard_normal(n)
+    rows = np.fft.fft(x.reshape(A, B), axis=0)                      # [tm][t]
+    tm, t = np.arange(A)[:, None], np.arange(B)[None, :]
+    y = np.fft.fft(rows * np.exp(-2j * np.pi * (tm * t % n) / n), axis=1)
+    got = y.T.reshape(-1)                                           # [j][tm]
+    ref = oracle.dft3d(x.reshape(n, 1, 1), -1, "direct").reshape(-1)
+    assert oracle.rel_l2(got, ref) < 1e-12
+
+
+def test_auto_schedule_of_other_lengths():
+    """AUTO keeps the pencil rotation where its rows start on 128-byte lines,
+    for small grids and for axes without a two-step pass, takes the slab
+    schedule where they do not, and either gives way to options that name a
+    pencil form; from 2.5 GiB up the pencil passes run in the cycle."""
+    def sched(shape, **kw):
+        return dft3d.describe(shape, "auto", **kw)["schedule"]
+    assert sched((375, 486, 400)) == "slab" and sched((105, 105, 105)) == "slab"
+    assert sched((324, 324, 324)) == "pencil" and sched((400, 400, 400)) == "pencil"
+    assert sched((61, 75, 90)) == "pencil" and sched((101, 375, 375)) == "pencil"
+    assert sched((675, 675, 675)) == "pencil" and sched((375, 375, 2048)) == "pencil"
+    for kw in ({"tile": 16}, {"radices": [3, 5, 5, 5]}, {"pencil_order": 0}):
+        assert sched((375, 375, 375), **kw) == "pencil", kw
+
+    def cycled(shape, **kw):
+        return [" cyc" in p["label"] for p in dft3d.describe(shape, "pencil", **kw)["passes"]]
+    assert cycled((1000, 1000, 1000)) == [True] * 3
+    assert cycled((1001, 1001, 1001)) == [True] * 3
+    assert cycled((1024, 1000, 900)) == [True] * 3
+    assert cycled((600, 600, 600)) == [False] * 3
+    assert cycled((1000, 1000, 1000), pencil_order=0) == [False] * 3
+
+
+@pytest.mark.parametrize("shape", [(1000, 700, 500), (1024, 1000, 900), (1001, 1009, 1013)])
+def test_cycled_order_of_other_lengths(shape):
+    """Each pass of the cycle reads and writes the documented orders: random
+    pencils of every pass land on (A, B, C) -> (B, C, A) -> (C, A, B) -> (A,
+    B, C), whatever the axis lengths."""
+    A, B, C = shape
+    d = dft3d.describe(shape, "pencil")
+    g = np.random.default_rng(A)
+    orders = [((0, 1, 2), (1, 2, 0), 2), ((1, 2, 0), (2, 0, 1), 0), ((2, 0, 1), (0, 1, 2), 1)]
+    for p, (order_in, order_out, axis) in zip(d["passes"], orders):
+        a = p["args"]
+        assert a["B"] * shape[axis] == A * B * C
+        # the pencil index runs over the slowest axis of the input fastest
+        fast, slow = order_in[0], order_in[1]
+        b = g.integers(0, a["B"], 200)
+        if a["s0"] < 0:
+            f0, f1, f2 = b % a["m0"], (b // a["m0"]) % a["m1"], b // (a["m0"] * a["m1"])
+        else:
+            f0, f1, f2 = b & a["m0"], (b >> a["s0"]) & a["m1"], b >> a["s1"]
+        j = g.integers(0, shape[axis], 200)
+        idx = {fast: b % shape[fast], slow: b // shape[fast], axis: j}
+
+        def place(order):
+            return (idx[order[0]] * shape[order[1]] + idx[order[1]]) * shape[order[2]] + idx[order[2]]
+        got_in = f2 * a["is"][2] + f1 * a["is"][1] + f0 * a["is"][0] + j * a["ijs"]
+        got_out = f2 * a["os"][2] + f1 * a["os"][1] + f0 * a["os"][0] + j * a["oks"]
+        assert (got_in == place(order_in)).all() and (got_out == place(order_out)).all()
+
+
+def bar(shape):
+    return 1e-6 * sum(np.log2(n) + 1 for n in shape if n > 1) / 18.0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("schedule", ["pencil", "slab"])
+@pytest.mark.parametrize("shape", [(6, 7, 30), (5, 17, 96), (125, 6, 16), (9, 143, 15),
+                                   (3, 375, 33), (32, 486, 5), (720, 3, 7), (1, 1000, 17),
+                                   (1008, 5, 1), (1024, 3, 5), (3, 1024, 6), (105, 49, 27)])
+def test_two_step_passes_on_the_gpu(shape, schedule):
+    """Smallest, largest and ragged cases of every order (rotating, rows,
+    columns), whole and ragged tiles, forward and inverse."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("case two-step", shape, schedule, flush=True)
+    x = inputs.uniform_c64(shape, 61)
+    for sign in (-1, 1):
+        y = dft3d.fftn(torch.from_numpy(x).cuda(), schedule=schedule, inverse=sign == 1)
+        torch.cuda.synchronize()
+        err = oracle.rel_l2(y.cpu().numpy(), oracle.dft3d(x.astype(np.complex128), sign, "direct"))
+        assert err <= bar(shape), (shape, schedule, sign, err)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(750, 720, 650), (225, 105, 75)])
+def test_auto_choices_of_other_lengths_on_the_gpu(shape):
+    """The cycle (above 2.5 GiB) and the slab choice of AUTO: sampled pencils
+    against the oracle's direct sums, and the round trip."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("case auto other lengths", shape, flush=True)
+    x = inputs.uniform_c64(shape, 62)
+    xt = torch.from_numpy(x).cuda()
+    y = dft3d.fftn(xt)
+    torch.cuda.synchronize()
+    g = np.random.default_rng(62)
+    k0 = np.concatenate([[0, shape[0] - 1], g.integers(0, shape[0], 4)])
+    k1 = np.concatenate([[0, shape[1] - 1], g.integers(0, shape[1], 4)])
+    got = y[torch.from_numpy(k0).cuda(), torch.from_numpy(k1).cuda(), :].cpu().numpy()
+    assert oracle.rel_l2(got, oracle.sample_pencils(x, k0, k1, -1)) <= bar(shape)
+    back = dft3d.ifftn(y) / x.size
+    rt = (torch.linalg.vector_norm(back - xt) / torch.linalg.vector_norm(xt)).item()
+    assert rt <= 2 * bar(shape)
