@@ -58,10 +58,12 @@ void free_workspace(dft3d_plan_s* p) {
   p->ws_owned = false;
 }
 
-// The twiddle table of a mixed-radix or Rader pass: (length, A, radix code).
+// The twiddle table of a mixed-radix, Rader or two-step Bluestein pass:
+// (length, A, radix code).
 using MixedKey = std::tuple<int64_t, int, uint64_t>;
 MixedKey mixed_key(const Pass& ps) {
   if (ps.k->rader) return {ps.rader_n - 1, 0, (uint64_t)ps.args.twp_mask};
+  if (ps.k->bluestein) return {ps.k->n, ps.k->two_step, 0};
   if (ps.k->two_step) return {ps.args.res_mask, ps.args.res_shift, 0};
   return {ps.args.res_mask, 0, (uint64_t)ps.args.twp_mask};
 }
@@ -86,10 +88,10 @@ int rebuild(dft3d_plan_s* p) {
 
   // one table per distinct root length (key n > 0) and per MFMA leaf
   // precision (key -precision, kLeafTableFloat2 slots of 16-bit values);
-  // Bluestein chirp and filter tables per length n (keys (1, n), (2, n),
-  // the filter stored right after the chirp)
+  // Bluestein chirp and filter tables per length n and kernel (the filter
+  // right after the chirp)
   std::map<int64_t, int64_t> offsets;
-  std::map<std::pair<int, int64_t>, int64_t> bl_offsets;
+  std::map<std::pair<int64_t, const KernelInfo*>, int64_t> bl_offsets;
   // mixed-radix twiddles (value: offset): staged passes per length n and
   // radix code (n, 0, code), two-step passes per length and split (n, A, 0)
   std::map<MixedKey, int64_t> mx_offsets;
@@ -127,6 +129,10 @@ int rebuild(dft3d_plan_s* p) {
       }
       continue;
     }
+    if (ps.k->bluestein && ps.k->two_step && !mx_offsets.count(mixed_key(ps))) {
+      mx_offsets[mixed_key(ps)] = total;  // the step twiddles of m
+      total += ps.k->n;
+    }
     for (int64_t len : {ps.tw_len, ps.twp_len}) {
       if (len > 0 && !offsets.count(len)) {
         offsets[len] = total;
@@ -137,11 +143,9 @@ int rebuild(dft3d_plan_s* p) {
       offsets[-ps.leaf] = total;
       total += kLeafTableFloat2;
     }
-    if (ps.k->bluestein && !bl_offsets.count({1, ps.bl_n})) {
-      bl_offsets[{1, ps.bl_n}] = total;
-      total += ps.bl_n;
-      bl_offsets[{2, ps.bl_n}] = total;
-      total += bluestein_length(ps.bl_n);
+    if (ps.k->bluestein && !bl_offsets.count({ps.bl_n, ps.k})) {
+      bl_offsets[{ps.bl_n, ps.k}] = total;
+      total += ps.bl_n + ps.k->n;
     }
   }
   std::vector<float2> host((size_t)total);
@@ -160,10 +164,10 @@ int rebuild(dft3d_plan_s* p) {
   }
   for (auto& kv : rd_offsets) make_rader_tables(kv.first, host.data() + kv.second);
   for (auto& kv : bl_offsets) {
-    if (kv.first.first == 1)
-      make_chirp(kv.first.second, host.data() + kv.second);
-    else
-      make_bluestein_filter(kv.first.second, host.data() + kv.second);
+    const int64_t n = kv.first.first;
+    const KernelInfo* k = kv.first.second;
+    make_chirp(n, host.data() + kv.second);
+    make_bluestein_filter(n, k->n, k->two_step, host.data() + kv.second + n);
   }
 
   float2* dev = nullptr;
@@ -198,8 +202,8 @@ int rebuild(dft3d_plan_s* p) {
         continue;
       }
       if (ps.k->bluestein) {  // roots of m; the chirp, with the filter right after it
-        tw.push_back(offsets[ps.tw_len]);
-        twp.push_back(bl_offsets[{1, ps.bl_n}]);
+        tw.push_back(ps.k->two_step ? mx_offsets[mixed_key(ps)] : offsets[ps.tw_len]);
+        twp.push_back(bl_offsets[{ps.bl_n, ps.k}]);
         continue;
       }
       tw.push_back(offsets[ps.tw_len]);

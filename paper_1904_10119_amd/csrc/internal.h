@@ -142,6 +142,10 @@ void make_rader_tables(int64_t n, float2* out);
 // The one-pass Bluestein axis kernel of convolution length m with the given
 // tile, else the length's default tile; null if none is compiled.
 const KernelInfo* find_bluestein_kernel(int m, int tile);
+// The Bluestein kernel with two-step FFTs for length n and the load and
+// store modes: the shortest convolution length >= 2 n compiled; null if
+// none (n > 512).
+const KernelInfo* find_bluestein_two_step_kernel(int64_t n, int lmode, int smode);
 // The fused volumetric two-axis kernel for split factor a, if compiled
 // (contig: V2 runs contiguous in memory; the persistent form if asked for;
 // shuffled: the finished axis left in the shuffled order).
@@ -177,7 +181,9 @@ int64_t bluestein_length(int64_t n);  // m: the power of two >= 2n - 1
 // (ns - 1) + (r - 1) ns + tm = w_{ns R}^{tm r} (r < R, tm < ns), from FP64.
 void make_mixed_twiddles(int64_t n, uint64_t code, float2* out);
 void make_chirp(int64_t n, float2* out);
-void make_bluestein_filter(int64_t n, float2* out);
+// a > 0: in the order of a two-step kernel of first step a, out[tm (m / a) +
+// k] = (H / m)[tm + a k]; else natural.
+void make_bluestein_filter(int64_t n, int64_t m, int a, float2* out);
 
 enum BufId { BUF_IN = 0, BUF_OUT = 1, BUF_WS = 2 };
 

@@ -34,6 +34,15 @@ namespace dft3d {
 // - i sum_k (x_k - x_{R-k}) sin(2 pi j k / R), and y_{R-j} with + i.
 template <int R>
 __device__ __forceinline__ void dft_odd(float2* x) {
+  if constexpr (R == 3) {  // one pair: its sine products fold into the sums
+    constexpr float sn = (float)unit_angle(1, 3).s;
+    const float2 s = cadd(x[1], x[2]), d = csub(x[1], x[2]);
+    const float2 a = make_float2(x[0].x - 0.5f * s.x, x[0].y - 0.5f * s.y);
+    x[0] = cadd(x[0], s);
+    x[1] = make_float2(a.x + sn * d.y, a.y - sn * d.x);
+    x[2] = make_float2(a.x - sn * d.y, a.y + sn * d.x);
+    return;
+  }
   constexpr int H = (R - 1) / 2;
   float2 s[H], d[H];
 #pragma unroll
@@ -68,10 +77,21 @@ constexpr int smallest_factor(int r) {
     if (r % f == 0) return f;
   return r;
 }
+// The whole power of r's smallest prime factor that divides r.
+constexpr int smallest_prime_power(int r) {
+  const int f = smallest_factor(r);
+  int p = 1;
+  for (; r % f == 0; r /= f) p *= f;
+  return p;
+}
 
 // Forward DFT of length R in registers: powers of two and odd primes
-// directly; other R = A B (A its smallest prime factor) by the four-step
-// identity of eq. (3) in registers: DFT_A over a for every b (input index
+// directly.  Coprime factors R = P Q (P the power of the smallest prime) by
+// the prime-factor index maps (Good's: input (Q p + P q) mod R, output k with
+// k mod P = p', k mod Q = q'), which need no twiddles: w_R^{(Q p + P q) k} =
+// w_P^{p k} w_Q^{q k}.  Against the four-step form with twiddles: 96 instead
+// of 148 instructions at 12, 282 / 358 at 21.  Prime powers (9, 25, 27) by
+// the four-step identity of eq. (3): DFT_A over a for every b (input index
 // b + B a), twiddle w_R^{b a'}, DFT_B over b (output index a' + A b').
 template <int R>
 __device__ __forceinline__ void dft_mixed(float2* x) {
@@ -79,6 +99,37 @@ __device__ __forceinline__ void dft_mixed(float2* x) {
     dft<R>(x);
   } else if constexpr (smallest_factor(R) == R) {
     dft_odd<R>(x);
+  } else if constexpr (smallest_prime_power(R) != R) {
+    constexpr int P = smallest_prime_power(R), Q = R / P;
+    float2 z[R];
+    static_for<Q>([&](auto qi) {
+      constexpr int q = decltype(qi)::value;
+      float2 s[P];
+      static_for<P>([&](auto pi) {
+        constexpr int p = decltype(pi)::value;
+        s[p] = x[(Q * p + P * q) % R];
+      });
+      dft_mixed<P>(s);
+#pragma unroll
+      for (int p = 0; p < P; ++p) z[p * Q + q] = s[p];
+    });
+    static_for<P>([&](auto pi) {
+      constexpr int p = decltype(pi)::value;
+      float2 s[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) s[q] = z[p * Q + q];
+      dft_mixed<Q>(s);
+      static_for<Q>([&](auto qi) {
+        constexpr int q = decltype(qi)::value;
+        // the k < R with k mod P = p and k mod Q = q
+        constexpr int k = [] {
+          int v = p;
+          while (v % Q != q) v += P;
+          return v;
+        }();
+        x[k] = s[q];
+      });
+    });
   } else {
     constexpr int A = smallest_factor(R), B = R / A;
     float2 z[R];

@@ -268,9 +268,11 @@ struct Builder {
   // One-pass Bluestein axis of length n (convolution length m) over the
   // pencils of fields f (bluestein.h documents the argument fields).
   void add_bluestein(int64_t n, const Field* f, int nf, int64_t ijs, int64_t oks,
-                     const std::string& label) {
-    const int64_t m = bluestein_length(n);
-    const KernelInfo* k = find_bluestein_kernel((int)m, opt.tile);
+                     const std::string& what, int lmode = MODE_ROW, int smode = MODE_COL) {
+    // two-step FFTs up to n = 512, power-of-two ones above
+    const KernelInfo* k = find_bluestein_two_step_kernel(n, lmode, smode);
+    if (!k) k = find_bluestein_kernel((int)bluestein_length(n), opt.tile);
+    const std::string label = what + " via " + std::to_string(k ? k->n : 0);
     if (!k) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;
       return;
@@ -281,8 +283,9 @@ struct Builder {
     p.args.ijs = ijs;
     p.args.oks = oks;
     p.args.res_mask = n;
+    p.args.res_shift = k->two_step;
     p.args.xcd_remap = opt.xcd_remap;
-    p.tw_len = m;
+    p.tw_len = k->two_step ? 0 : k->n;
     p.bl_n = n;
     p.label = label;
     passes.push_back(p);
@@ -315,7 +318,9 @@ struct Builder {
   // (mixed_kernel.h documents the argument fields).
   void add_mixed(int64_t n, const Field* f, int nf, int64_t ijs, int64_t oks,
                  const std::string& label, int lmode = MODE_ROW, int smode = MODE_COL) {
-    const bool asked = opt.radices && radix_code_length(opt.radices) == n;
+    // (a sequence equal to the length's default keeps its default kernel)
+    const bool asked = opt.radices && radix_code_length(opt.radices) == n &&
+                       opt.radices != mixed_radix_code(n);
     const uint64_t code = asked ? opt.radices : mixed_radix_code(n);
     // two register steps where the length splits into them, the staged
     // kernel for other lengths, an asked-for tile or radix sequence
@@ -533,8 +538,8 @@ void pencil_axis(Builder& b, const int64_t cur[3], bool split, int axis) {
   if (!is_pow2(n)) {
     // Bluestein (bluestein.h): the whole axis in one rotate-on-write pass
     Field f[1] = {{B, n, 1}};
-    std::snprintf(lab, sizeof lab, "pencil%d DFT%lld via %lld x%lld rot", axis, (long long)n,
-                  (long long)bluestein_length(n), (long long)B);
+    std::snprintf(lab, sizeof lab, "pencil%d DFT%lld x%lld rot", axis, (long long)n,
+                  (long long)B);
     b.add_bluestein(n, f, 1, 1, B, lab);
     return;
   }
@@ -668,8 +673,7 @@ void axis_pass(Builder& b, int64_t n, int lmode, int smode, const Field* f, int 
     std::snprintf(lab, sizeof lab, "%s rader", label);
     b.add_rader(n, f, nf, ijs, oks, lab);
   } else {
-    std::snprintf(lab, sizeof lab, "%s via %lld", label, (long long)bluestein_length(n));
-    b.add_bluestein(n, f, nf, ijs, oks, lab);
+    b.add_bluestein(n, f, nf, ijs, oks, label, lmode, smode);
   }
 }
 
@@ -1145,7 +1149,8 @@ void describe_list(std::ostringstream& os, const std::vector<Pass>& passes) {
     }
     os << "],\"split\":[";
     if (p.k->two_step)  // two-step passes: the register DFTs the radices are grouped into
-      os << p.args.res_shift << "," << p.args.res_mask / p.args.res_shift;
+      os << p.k->two_step << ","
+         << (p.k->bluestein ? p.k->n : p.args.res_mask) / p.k->two_step;
     os << "]"
        << ",\"mfma_leaf\":" << p.k->mfma_leaf << ",\"threads\":" << p.k->threads
        << ",\"lds_bytes\":" << p.k->lds_bytes << ",\"pencils\":" << p.args.B

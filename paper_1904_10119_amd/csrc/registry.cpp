@@ -24,6 +24,10 @@ void register_kernels_mixed_fixed(std::vector<KernelInfo>& v);
 void register_kernels_rader(std::vector<KernelInfo>& v);
 void register_kernels_rader_fixed(std::vector<KernelInfo>& v);
 void register_kernels_halves(std::vector<KernelInfo>& v);
+void register_kernels_bluestein_two_step_a(std::vector<KernelInfo>& v);
+void register_kernels_bluestein_two_step_b(std::vector<KernelInfo>& v);
+void register_kernels_bluestein_two_step_c(std::vector<KernelInfo>& v);
+void register_kernels_bluestein_two_step_d(std::vector<KernelInfo>& v);
 void register_kernels_two_step_a(std::vector<KernelInfo>& v);
 void register_kernels_two_step_b(std::vector<KernelInfo>& v);
 void register_kernels_two_step_c(std::vector<KernelInfo>& v);
@@ -52,6 +56,10 @@ const std::vector<KernelInfo>& kernel_registry() {
     register_kernels_rader(v);
     register_kernels_rader_fixed(v);
     register_kernels_halves(v);
+    register_kernels_bluestein_two_step_a(v);
+    register_kernels_bluestein_two_step_b(v);
+    register_kernels_bluestein_two_step_c(v);
+    register_kernels_bluestein_two_step_d(v);
     register_kernels_two_step_a(v);
     register_kernels_two_step_b(v);
     register_kernels_two_step_c(v);
@@ -136,7 +144,7 @@ const KernelInfo* find_mixed_kernel(int64_t n, uint64_t code, int tile, int lmod
 
 const KernelInfo* find_two_step_kernel(int64_t n, int lmode, int smode) {
   for (const KernelInfo& k : kernel_registry())
-    if (k.two_step && k.fixed_n == n && k.lmode == lmode && k.smode == smode) return &k;
+    if (k.two_step && k.mixed && k.fixed_n == n && k.lmode == lmode && k.smode == smode) return &k;
   return nullptr;
 }
 
@@ -244,11 +252,20 @@ bool rader_length(int64_t n, bool any_kernel) {
 const KernelInfo* find_bluestein_kernel(int m, int tile) {
   const KernelInfo* first = nullptr;
   for (const KernelInfo& k : kernel_registry())
-    if (k.bluestein && k.n == m) {
+    if (k.bluestein && !k.two_step && k.n == m) {
       if (k.tile == tile) return &k;
       if (!first) first = &k;
     }
   return first;
+}
+
+const KernelInfo* find_bluestein_two_step_kernel(int64_t n, int lmode, int smode) {
+  const KernelInfo* best = nullptr;
+  for (const KernelInfo& k : kernel_registry())
+    if (k.bluestein && k.two_step && k.n >= 2 * n && k.lmode == lmode && k.smode == smode &&
+        (!best || k.n < best->n))
+      best = &k;
+  return best;
 }
 
 const KernelInfo* find_fused_axes_kernel(int a, int contig, int persistent, int kind) {

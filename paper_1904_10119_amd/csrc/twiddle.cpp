@@ -204,8 +204,7 @@ void make_chirp(int64_t n, float2* out) {
   }
 }
 
-void make_bluestein_filter(int64_t n, float2* out) {
-  const int64_t m = bluestein_length(n);
+void make_bluestein_filter(int64_t n, int64_t m, int a, float2* out) {
   // wrapped filter h[d] = conj(w[|d|]) at d mod m, in FP64
   std::vector<double> hr(m, 0.0), hi(m, 0.0);
   for (int64_t d = 0; d < n; ++d) {
@@ -228,7 +227,8 @@ void make_bluestein_filter(int64_t n, float2* out) {
       yr += hr[d] * rc[e] + hi[d] * rs[e];
       yi += hi[d] * rc[e] - hr[d] * rs[e];
     }
-    out[l] = make_float2((float)(yr / (double)m), (float)(yi / (double)m));
+    const int64_t at = a ? l % a * (m / a) + l / a : l;
+    out[at] = make_float2((float)(yr / (double)m), (float)(yi / (double)m));
   }
 }
 
