@@ -33,19 +33,23 @@ int device_cu_count();
 
 namespace {
 
-int batch_tile_for(int n) {
+template <int LM>
+int batch_tile_of(int n) {
   switch (n) {
-    case 1: return batch_tile<1>();
-    case 2: return batch_tile<2>();
-    case 4: return batch_tile<4>();
-    case 8: return batch_tile<8>();
-    case 16: return batch_tile<16>();
-    case 32: return batch_tile<32>();
-    case 64: return batch_tile<64>();
-    case 128: return batch_tile<128>();
-    case 256: return batch_tile<256>();
+    case 1: return batch_tile<1, LM>();
+    case 2: return batch_tile<2, LM>();
+    case 4: return batch_tile<4, LM>();
+    case 8: return batch_tile<8, LM>();
+    case 16: return batch_tile<16, LM>();
+    case 32: return batch_tile<32, LM>();
+    case 64: return batch_tile<64, LM>();
+    case 128: return batch_tile<128, LM>();
+    case 256: return batch_tile<256, LM>();
     default: return 0;
   }
+}
+int batch_tile_for(int n, int lmode) {
+  return lmode == MODE_ROW ? batch_tile_of<MODE_ROW>(n) : batch_tile_of<MODE_COL>(n);
 }
 
 // One launch of the level form: the 1D items or one class of plane items of
@@ -67,7 +71,7 @@ bool batchable(const std::vector<Pass>& passes, bool persistent) {
       continue;
     }
     if (ps.k->n > kBatchMaxN || ps.k->post_twiddle) return false;
-    if (batch_tile_for(ps.k->n) == 0) return false;
+    if (batch_tile_for(ps.k->n, ps.k->lmode) == 0) return false;
   }
   return true;
 }
@@ -107,7 +111,7 @@ int batch_layout(const std::vector<const std::vector<Pass>*>& lists, std::vector
         if (planes) {
           it.ntiles = ps.args.B;
         } else {
-          const int T = batch_tile_for(it.n);
+          const int T = batch_tile_for(it.n, it.lmode);
           it.ntiles = (ps.args.B + T - 1) / T;
         }
         it.first = first;
@@ -589,7 +593,7 @@ std::string batch_describe(const std::vector<const std::vector<Pass>*>& lists,
     os << (k ? "," : "") << "{\"problem\":" << item_plan[k] << ",\"pass\":" << item_pass[k]
        << ",\"first\":" << it.first << ",\"ntiles\":" << it.ntiles << ",\"dep\":" << it.dep
        << ",\"n\":" << it.n << ",\"n1\":" << it.n1 << ",\"pencils\":" << it.a.B
-       << ",\"tile\":" << (it.n1 ? 1 : batch_tile_for(it.n)) << "}";
+       << ",\"tile\":" << (it.n1 ? 1 : batch_tile_for(it.n, it.lmode)) << "}";
   }
   os << "],\"levels\":[";
   for (size_t k = 0; k < levels.size(); ++k) {

@@ -24,16 +24,26 @@
 
 #include "pass_kernel.h"
 #include "plane_kernel.h"
+#include "two_step_kernel.h"
 
 namespace dft3d {
 
-// Workgroup size of the batched kernel; tile = kBatchThreads / P(n) pencils.
+// Workgroup size of the batched kernel.
 constexpr int kBatchThreads = 256;
 // Longest transform length a batched item may have.
 constexpr int kBatchMaxN = 256;
 
-template <int N> constexpr int batch_tile() {
-  return kBatchThreads / (N / Blocking<N>::E);
+// Contiguous axes from length 16 up run in the two register steps a plan's
+// own passes take (a butterfly of step 1 a thread); strided axes, whose row
+// segments are the tile, and shorter lengths run the pass kernel's stages in
+// its larger tiles (96 problems of {32, 64, 128}^3, two steps everywhere: 286
+// against 280 us).
+template <int N, int LM> constexpr bool batch_two_step() { return N >= 16 && LM == MODE_ROW; }
+template <int N, int LM> constexpr int batch_tile() {
+  if constexpr (batch_two_step<N, LM>())
+    return kBatchThreads / (N / two_step_split(N));
+  else
+    return kBatchThreads / (N / Blocking<N>::E);
 }
 
 struct BatchItem {
@@ -68,30 +78,39 @@ struct BatchState {
 };
 
 // LDS bytes of the largest tile the batched kernel runs.
-template <int N> constexpr int batch_lds_elems() {
-  return num_stages<Blocking<N>>() > 1 ? batch_tile<N>() * lds_pencil_stride<N, batch_tile<N>()>()
-                                       : 1;
-}
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
+template <int N> constexpr int batch_lds_elems() {
+  constexpr int T = batch_tile<N, MODE_COL>();
+  return cmax(batch_tile<N, MODE_ROW>() *
+                  two_step_stride(two_step_split(N), N / two_step_split(N)),
+              num_stages<Blocking<N>>() > 1 ? T * lds_pencil_stride<N, T>() : 1);
+}
 constexpr int kBatchLdsElems =
     cmax(cmax(cmax(batch_lds_elems<256>(), batch_lds_elems<128>()), batch_lds_elems<64>()),
          cmax(batch_lds_elems<32>(), batch_lds_elems<16>()));
 
 template <int N, int LM, int SM>
 __device__ __forceinline__ void batch_tile_run(const BatchItem& it, int64_t tile, float2* lds) {
-  using BL = Blocking<N>;
-  constexpr int E = BL::E;
-  constexpr int P = N / E;
-  constexpr int T = batch_tile<N>();
-  constexpr int NST = num_stages<BL>();
-  constexpr int SQ = lds_pencil_stride<N, T>();
+  constexpr int T = batch_tile<N, LM>();
   const int tid = threadIdx.x;
-  int q, p;
-  thread_map<(NST > 1 ? LM : SM), T, P>(tid, q, p);
-  float2 v[E];
-  load_tile<N, T, E, P, LM, 0>(v, it.src, it.a, tile, q, p);
-  transform_store_tile<N, BL, T, LM, SM, 0, 0, E, P, SQ>(v, it.dst, it.tw, nullptr, lds, it.a,
-                                                         tile, tid, q, p);
+  if constexpr (batch_two_step<N, LM>()) {
+    constexpr int A = two_step_split(N), B = N / A;
+    static_assert(T * B == kBatchThreads && A <= B, "a butterfly of step 1 a thread");
+    two_step_first<A, B, T, LM, kRoots>(it.src, it.a, tile, lds, tid);
+    two_step_second<A, B, T, SM, kRoots>(it.dst, it.tw, it.a, tile, lds, tid);
+  } else {
+    using BL = Blocking<N>;
+    constexpr int E = BL::E;
+    constexpr int P = N / E;
+    constexpr int NST = num_stages<BL>();
+    constexpr int SQ = lds_pencil_stride<N, T>();
+    int q, p;
+    thread_map<(NST > 1 ? LM : SM), T, P>(tid, q, p);
+    float2 v[E];
+    load_tile<N, T, E, P, LM, 0>(v, it.src, it.a, tile, q, p);
+    transform_store_tile<N, BL, T, LM, SM, 0, 0, E, P, SQ>(v, it.dst, it.tw, nullptr, lds, it.a,
+                                                           tile, tid, q, p);
+  }
 }
 
 template <int N>

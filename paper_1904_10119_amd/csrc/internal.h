@@ -79,6 +79,9 @@ const std::vector<KernelInfo>& kernel_registry();
 const KernelInfo* find_move_only_kernel(const KernelInfo* k, int mode);
 const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_twiddle,
                               int persistent, int nontemporal);
+// The two-step kernel (two_step_kernel.h) for an FP32 pass of a power of two
+// over `pencils` pencils, or null.
+const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, int smode);
 // The two-halves pass of length n (halves_kernel.h) with the given load and
 // store orders and form, or null if none is compiled.
 const KernelInfo* find_halves_kernel(int n, int lmode, int smode, int persistent,

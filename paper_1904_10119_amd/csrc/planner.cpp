@@ -71,8 +71,8 @@ constexpr int64_t kGroupBytes = int64_t(256) << 20;
 // one-tile-per-workgroup kernels with ordinary ones.  Automatic mode uses
 // the persistent form with streaming accesses for arrays that cannot stay
 // in the caches, and the one-tile form with ordinary accesses otherwise.
-const KernelInfo* pick_kernel(int n, int lmode, int smode, int tw, const Options& opt,
-                              int64_t total_points) {
+const KernelInfo* pick_kernel(int n, int64_t pencils, int lmode, int smode, int tw,
+                              const Options& opt, int64_t total_points) {
   struct Choice {
     int pers, nt;
   };
@@ -90,7 +90,15 @@ const KernelInfo* pick_kernel(int n, int lmode, int smode, int tw, const Options
   // except that the strided 2048 pass has one tile per workgroup only (its
   // persistent form measured slower: 5.42 against 5.29 ms per launch at
   // 2048 x 1024 x 512)
-  if (opt.halves && tw == 0) {
+  // and except where the halves tiles (32768 points, one workgroup a CU)
+  // would leave CUs idle: the whole-length kernels then run more, smaller
+  // ones (1024 x 16 x 64, depth pass 32 / 128 workgroups: 19.2 -> 9.1 us,
+  // 2048 x 64 x 32 26.8 -> 18.6; at 256 halves tiles they are the faster
+  // form again: 1024 x 128 x 64 30.6 against 35.2).  Arrays up to 2^16
+  // points keep the halves kernels.
+  const bool idle = opt.nontemporal == 2 && opt.tile <= 0 &&
+                    total_points > (int64_t(1) << 16) && pencils < 256 * (32768 / n);
+  if (opt.halves && tw == 0 && !idle) {
     const bool big = total_points * 8 >= kStreamBytes;
     const int nt = opt.nontemporal == 2 ? (big ? 1 : 0) : opt.nontemporal;
     const int pers = opt.persistent && (opt.nontemporal != 2 || big) &&
@@ -107,9 +115,14 @@ const KernelInfo* pick_kernel(int n, int lmode, int smode, int tw, const Options
       if (const KernelInfo* k = find_kernel(n, 32, lmode, smode, tw, pers, nt)) return k;
     if (opt.tile > 0) {
       if (const KernelInfo* k = find_kernel(n, opt.tile, lmode, smode, tw, pers, nt)) return k;
+    } else if (!pers && !nt && !tw) {
+      if (const KernelInfo* k = find_two_step_power_kernel(n, pencils, lmode, smode)) return k;
     }
-    if (const KernelInfo* k = find_kernel(n, default_tile(n), lmode, smode, tw, pers, nt))
-      return k;
+    // half the default pencils of the longest lengths where fewer than 256
+    // workgroups would leave CUs idle (2048 x 32 x 32: 14.5 us a pass)
+    int tile = default_tile(n);
+    if (n >= 2048 && !pers && pencils < 256 * tile) tile /= 2;
+    if (const KernelInfo* k = find_kernel(n, tile, lmode, smode, tw, pers, nt)) return k;
   }
   // any available tile for this length
   const int nt = order[nchoice - 1].nt;
@@ -117,7 +130,7 @@ const KernelInfo* pick_kernel(int n, int lmode, int smode, int tw, const Options
     if (k.n == n && k.lmode == lmode && k.smode == smode && k.post_twiddle == tw &&
         k.persistent == 0 && k.nontemporal == nt && k.precision == 0 && k.plane_rows == 0 &&
         k.fused_axes == 0 && k.bluestein == 0 && k.mixed == 0 && k.rader == 0 &&
-        k.halves == 0 && k.move_only == 0)
+        k.halves == 0 && k.two_step == 0 && k.move_only == 0)
       return &k;
   return nullptr;
 }
@@ -224,7 +237,9 @@ struct Builder {
         k = find_mfma_kernel(n, lmode, smode, opt.precision, pers, 0, opt.tile);
       if (k) leaf = opt.precision;
     }
-    if (!k) k = pick_kernel(n, lmode, smode, tw, opt, total_points);
+    int64_t pencils = 1;
+    for (int i = 0; i < nf; ++i) pencils *= f[i].count;
+    if (!k) k = pick_kernel(n, pencils, lmode, smode, tw, opt, total_points);
     if (!k) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;
       return;
@@ -586,7 +601,8 @@ int pencil_order(const int64_t n[3], const Options& opt) {
 // One rotate-on-write pass of the cycled order.  FP32 passes of length up
 // to 1024 take the one-tile kernel (two workgroups' tiles in flight per CU
 // instead of one persistent workgroup prefetching): measured in this order
-// 1024^3 10.75 -> 10.44 ms, 512^3 1.29 -> 1.26 ms; the persistent form
+// 1024^3 10.75 -> 10.44 ms, 512^3 1.29 -> 1.26 ms, and in two register steps
+// (find_two_step_power_kernel) 10.26 and 1.22 ms; the persistent form
 // stays where streaming is forced on (nontemporal = 1) and for longer
 // lengths (the 2048 pass as persistent halves).
 void add_cycled(Builder& b, int len, const Field* f, int64_t oks, const char* lab) {
@@ -1150,7 +1166,7 @@ void describe_list(std::ostringstream& os, const std::vector<Pass>& passes) {
     os << "],\"split\":[";
     if (p.k->two_step)  // two-step passes: the register DFTs the radices are grouped into
       os << p.k->two_step << ","
-         << (p.k->bluestein ? p.k->n : p.args.res_mask) / p.k->two_step;
+         << (p.k->mixed ? p.args.res_mask : p.k->n) / p.k->two_step;
     os << "]"
        << ",\"mfma_leaf\":" << p.k->mfma_leaf << ",\"threads\":" << p.k->threads
        << ",\"lds_bytes\":" << p.k->lds_bytes << ",\"pencils\":" << p.args.B

@@ -28,6 +28,7 @@ void register_kernels_bluestein_two_step_a(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_b(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_c(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_d(std::vector<KernelInfo>& v);
+void register_kernels_two_step_power(std::vector<KernelInfo>& v);
 void register_kernels_two_step_a(std::vector<KernelInfo>& v);
 void register_kernels_two_step_b(std::vector<KernelInfo>& v);
 void register_kernels_two_step_c(std::vector<KernelInfo>& v);
@@ -60,6 +61,7 @@ const std::vector<KernelInfo>& kernel_registry() {
     register_kernels_bluestein_two_step_b(v);
     register_kernels_bluestein_two_step_c(v);
     register_kernels_bluestein_two_step_d(v);
+    register_kernels_two_step_power(v);
     register_kernels_two_step_a(v);
     register_kernels_two_step_b(v);
     register_kernels_two_step_c(v);
@@ -78,7 +80,40 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
         k.post_twiddle == post_twiddle && k.persistent == persistent &&
         k.nontemporal == nontemporal && k.precision == 0 && k.plane_rows == 0 &&
         k.fused_axes == 0 && k.bluestein == 0 && k.mixed == 0 && k.rader == 0 &&
-        k.halves == 0 && k.move_only == 0)
+        k.halves == 0 && k.two_step == 0 && k.move_only == 0)
+      return &k;
+  return nullptr;
+}
+
+// Measured on MI355X, one-tile pass kernel / two-step kernel per launch, in
+// us: length 16 (16 x 32 x 512) 4.2 / 3.3, 32 (32^3) 4.4 / 3.0, 64 (64^3) 4.4
+// / 3.7, 128 (128^3) 9.7 / 8.5, 256 (256^3 rows, columns) 56.9, 44.8 / 54.7,
+// 44.0, 512 (512^3) 1252 / 1216 (whole transform), 1024 (64 x 1024 x 1024)
+// 251 / 246 and 1024^3 10.49 / 10.26 ms (whole transform).
+// Tiles of 16 pencils, with these exceptions:
+//  - 64 from 2^22 points up 32 pencils (64 x 512 x 512 43.0 / 41.9);
+//  - 128 from 2^24 points up the 32-pencil pass kernel (512 x 512 x 128 rows
+//    95.8 against 101 us with two steps in 32 pencils, 104 in 16);
+//  - 256 above 2^25 points 32 pencils (1024 x 512 x 256 437 / 412; below, 16
+//    are faster: 128 x 1024 x 256 rows 97.6 against 103.7);
+//  - 16, 32 and 64 along strided axes from 2^21 points up the pass kernel,
+//    whose 256, 128 or 64 pencils are long row segments (16 x 512 x 512 depth
+//    11.8 against 12.7, 32 x 256 x 512 10.9 against 13.0);
+//  - from 256 up, where tiles of 16 are at most 512 (two a CU), 8 pencils
+//    (16 x 256 x 256 8.3 / 7.2, 16 x 64 x 1024 12.2 / 9.1, 16 x 512 x 512 rows
+//    15.3 / 14.2; tiles of 4 gain no more, and at 1024 tiles 16 are faster:
+//    32 x 512 x 512 rows 32.4 against 34.7).
+const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, int smode) {
+  const int64_t points = pencils * n;
+  int tile = 16;
+  if (n == 64 && points >= (int64_t(1) << 22)) tile = 32;
+  if (n == 128 && points >= (int64_t(1) << 24)) return nullptr;
+  if (n == 256 && points > (int64_t(1) << 25)) tile = 32;
+  if (n <= 64 && lmode == MODE_COL && points >= (int64_t(1) << 21)) return nullptr;
+  if (n >= 256 && pencils <= 16 * 512) tile = 8;
+  for (const KernelInfo& k : kernel_registry())
+    if (k.two_step && !k.mixed && !k.bluestein && !k.move_only && k.n == n && k.tile == tile &&
+        k.lmode == lmode && k.smode == smode)
       return &k;
   return nullptr;
 }
@@ -100,7 +135,7 @@ const KernelInfo* find_move_only_kernel(const KernelInfo* k, int mode) {
   if (k->halves && mode == 1)
     return find_halves_kernel(k->n, k->lmode, k->smode, k->persistent, k->nontemporal, 1);
   for (const KernelInfo& c : kernel_registry()) {
-    if (c.move_only != mode || c.halves) continue;
+    if (c.move_only != mode || c.halves || (mode == 1 && c.two_step != k->two_step)) continue;
     if (mode == 2 && c.n == k->n) return &c;
     if (mode == 1 && c.n == k->n && c.tile == k->tile && c.lmode == k->lmode &&
         c.smode == k->smode && c.post_twiddle == k->post_twiddle &&

@@ -45,113 +45,89 @@ __host__ __device__ constexpr int two_step_stride(int a, int b) {
   return (a * two_step_pitch(b)) | 1;
 }
 
-// id = quot d + rem for 0 <= id < 1600 and 1 <= d <= 40 by a multiplication
-// with m = ceil(65536 / d) (exact while id (m d - 65536) < 65536).
-__device__ __forceinline__ void split_id(int id, int d, int m, int& quot, int& rem) {
-  quot = (id * m) >> 16;
-  rem = id - quot * d;
-}
-constexpr int kTwoStepMaxIds = 1600;
+// FORM bits of a two-step kernel: kRoots reads w_n^{tm j} from a table of the
+// roots of length n at tm j (the power-of-two passes, whose tables the other
+// power-of-two kernels share); kMove leaves the DFTs and twiddles out (the
+// move-only option).
+constexpr int kRoots = 1, kMove = 2;
 
-// Step 1 of radix R over the tile: B butterflies a pencil.
-template <int R, int T, int LM>
+// Step 1 of radix R over the tile: B butterflies a pencil, one a thread.
+template <int R, int B, int T, int LM, int FORM>
 __device__ __forceinline__ void two_step_first(const float2* src, const PassArgs& a,
-                                               int64_t tile, float2* lds, int B, int tid,
-                                               int th) {
-  const int pitch = two_step_pitch(B), sq = two_step_stride(R, B);
-  const int mb = (65535 + B) / B;
-  for (int id = tid; id < T * B; id += th) {
-    int q, t;
-    if constexpr (LM == MODE_ROW) {
-      split_id(id, B, mb, q, t);
-    } else {
-      q = id % T;
-      t = id / T;
-    }
-    // pencils past the end of a ragged last tile read the last pencil
-    int64_t b = tile * T + q;
-    b = b < a.B ? b : a.B - 1;
-    const float2* s =
-        src + pencil_offset_any(b, a.m0, a.m1, a.s0, a.s1, a.is0, a.is1, a.is2);
-    float2 v[R];
-    if constexpr (LM == MODE_ROW) {
-      s += t;
+                                               int64_t tile, float2* lds, int tid) {
+  constexpr int pitch = two_step_pitch(B), sq = two_step_stride(R, B);
+  if (tid >= T * B) return;
+  const int q = LM == MODE_ROW ? tid / B : tid % T;
+  const int t = LM == MODE_ROW ? tid % B : tid / T;
+  // pencils past the end of a ragged last tile read the last pencil
+  int64_t b = tile * T + q;
+  b = b < a.B ? b : a.B - 1;
+  const float2* s = src + pencil_offset_any(b, a.m0, a.m1, a.s0, a.s1, a.is0, a.is1, a.is2);
+  float2 v[R];
+  if constexpr (LM == MODE_ROW) {
+    s += t;
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = s[r * B];
-    } else {
-      s += t * a.ijs;
-      const int64_t step = B * a.ijs;
+    for (int r = 0; r < R; ++r) v[r] = s[r * B];
+  } else {
+    s += t * a.ijs;
+    const int64_t step = B * a.ijs;
 #pragma unroll
-      for (int r = 0; r < R; ++r) v[r] = s[r * step];
-    }
-    if (a.conj_in) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[r].y = -v[r].y;
-    }
-    dft_mixed<R>(v);
-    float2* w = lds + q * sq + t;
-#pragma unroll
-    for (int r = 0; r < R; ++r) w[r * pitch] = v[r];
+    for (int r = 0; r < R; ++r) v[r] = s[r * step];
   }
+  if (a.conj_in) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r].y = -v[r].y;
+  }
+  if constexpr (!(FORM & kMove)) dft_mixed<R>(v);
+  float2* w = lds + q * sq + t;
+#pragma unroll
+  for (int r = 0; r < R; ++r) w[r * pitch] = v[r];
 }
 
-// Step 2 of radix R over the tile (A butterflies a pencil) and the store.
-// The first butterfly's twiddles are read before the barrier that ends
-// step 1 where they fit in registers beside its data.
-template <int R, int T, int SM>
+// Step 2 of radix R over the tile (A butterflies a pencil, one a thread) and
+// the store.  The twiddles are read before the barrier that ends step 1
+// where they fit in registers beside the data.
+template <int A, int R, int T, int SM, int FORM>
 __device__ __forceinline__ void two_step_second(float2* dst, const float2* __restrict__ tw,
                                                 const PassArgs& a, int64_t tile,
-                                                const float2* lds, int A, int tid, int th) {
-  constexpr bool EARLY = R <= 16;
-  const int pitch = two_step_pitch(R), sq = two_step_stride(A, R);
-  const int ma = (65535 + A) / A;
-  auto place = [&](int id, int& q, int& tm) {
-    if constexpr (SM == MODE_ROW) {
-      split_id(id, A, ma, q, tm);
-    } else {
-      q = id % T;
-      tm = id / T;
-    }
-  };
-  int q, tm;
-  place(tid, q, tm);
+                                                const float2* lds, int tid) {
+  constexpr bool MV = (FORM & kMove) != 0, EARLY = R <= 16 && !MV;
+  constexpr int pitch = two_step_pitch(R), sq = two_step_stride(A, R);
+  const int q = SM == MODE_ROW ? tid / A : tid % T;
+  const int tm = SM == MODE_ROW ? tid % A : tid / T;
   float2 w[R];
-  if constexpr (EARLY) {
-    if (tid < T * A) {
+  auto twiddles = [&] {
 #pragma unroll
-      for (int j = 1; j < R; ++j) w[j] = tw[tm * R + j];
-    }
+    for (int j = 1; j < R; ++j) w[j] = tw[(FORM & kRoots) ? tm * j : tm * R + j];
+  };
+  if constexpr (EARLY) {
+    if (tid < T * A) twiddles();
   }
   __syncthreads();  // every output of step 1 is in LDS
-  for (int id = tid; id < T * A; id += th) {
-    if (id != tid || !EARLY) {
-      place(id, q, tm);
+  if (tid >= T * A) return;
+  if constexpr (!EARLY && !MV) twiddles();
+  const float2* row = lds + q * sq + tm * pitch;
+  float2 v[R];
+  v[0] = row[0];
 #pragma unroll
-      for (int j = 1; j < R; ++j) w[j] = tw[tm * R + j];
-    }
-    const float2* row = lds + q * sq + tm * pitch;
-    float2 v[R];
-    v[0] = row[0];
+  for (int j = 1; j < R; ++j) v[j] = MV ? row[j] : cmul(row[j], w[j]);
+  if constexpr (!MV) dft_mixed<R>(v);
+  if (a.conj_out) {
 #pragma unroll
-    for (int j = 1; j < R; ++j) v[j] = cmul(row[j], w[j]);
-    dft_mixed<R>(v);
-    if (a.conj_out) {
+    for (int j = 0; j < R; ++j) v[j].y = -v[j].y;
+  }
+  const int64_t b = tile * T + q;
+  if (b < a.B) {
+    float2* d = dst + pencil_offset_any(b, a.m0, a.m1, a.s0, a.s1, a.os0, a.os1, a.os2);
+    if constexpr (SM == MODE_ROW) {
+      d += tm;
 #pragma unroll
-      for (int j = 0; j < R; ++j) v[j].y = -v[j].y;
-    }
-    const int64_t b = tile * T + q;
-    if (b < a.B) {
-      float2* d = dst + pencil_offset_any(b, a.m0, a.m1, a.s0, a.s1, a.os0, a.os1, a.os2);
-      if constexpr (SM == MODE_ROW) {
-        d += tm;
+      for (int j = 0; j < R; ++j) d[j * A] = v[j];
+    } else {
+      d += tm * a.oks;
+      const int64_t step = A * a.oks;
 #pragma unroll
-        for (int j = 0; j < R; ++j) d[j * A] = v[j];
-      } else {
-        d += tm * a.oks;
-        const int64_t step = A * a.oks;
-#pragma unroll
-        for (int j = 0; j < R; ++j) d[j * step] = v[j];
-      }
+      for (int j = 0; j < R; ++j) d[j * step] = v[j];
     }
   }
 }
@@ -159,30 +135,30 @@ __device__ __forceinline__ void two_step_second(float2* dst, const float2* __res
 // One workgroup per tile of T pencils; the length A * B, the tile and the
 // orders are compile-time constants (sizes and LDS offsets fold, no radix
 // switch, and each length has its own register count).
-template <int A, int B, int T, int TH, int LM, int SM>
+template <int A, int B, int T, int TH, int LM, int SM, int FORM>
 __global__ void __launch_bounds__(TH)
 fft_two_step_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
                    const float2* __restrict__ twp, const PassArgs a) {
   __shared__ float2 lds[T * two_step_stride(A, B)];
   const int tid = threadIdx.x;
   const int64_t tile = tile_index(blockIdx.x, gridDim.x, a.xcd_remap);
-  two_step_first<A, T, LM>(src, a, tile, lds, B, tid, TH);
-  two_step_second<B, T, SM>(dst, tw, a, tile, lds, A, tid, TH);
+  two_step_first<A, B, T, LM, FORM>(src, a, tile, lds, tid);
+  two_step_second<A, B, T, SM, FORM>(dst, tw, a, tile, lds, tid);
 }
 
 // Threads of a two-step workgroup: a butterfly of step 1 for each (at most
 // 40 x 16 or 8 x 64).
 constexpr int two_step_threads(int b, int t) { return (t * b + 63) / 64 * 64; }
 
-template <int A, int B, int T, int LM, int SM>
+template <int A, int B, int T, int LM, int SM, int FORM>
 hipError_t launch_two_step(const PassArgs& a, const float2* src, float2* dst, const float2* tw,
                            const float2* twp, hipStream_t stream) {
   const int64_t blocks = (a.B + T - 1) / T;
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  if (a.res_shift != A || a.res_mask != A * B) return hipErrorInvalidValue;
+  if (FORM == 0 && (a.res_shift != A || a.res_mask != A * B)) return hipErrorInvalidValue;
   constexpr int TH = two_step_threads(B, T);
-  hipLaunchKernelGGL((fft_two_step_kernel<A, B, T, TH, LM, SM>), dim3((unsigned)blocks),
+  hipLaunchKernelGGL((fft_two_step_kernel<A, B, T, TH, LM, SM, FORM>), dim3((unsigned)blocks),
                      dim3(TH), 0, stream, src, dst, tw, twp, a);
   return hipGetLastError();
 }
@@ -190,13 +166,36 @@ hipError_t launch_two_step(const PassArgs& a, const float2* src, float2* dst, co
 template <int A, int B, int T, int LM, int SM>
 KernelInfo kernel_info_two_step() {
   constexpr int LDS = T * two_step_stride(A, B) * 8, TH = two_step_threads(B, T);
-  static_assert(LDS <= 160 * 1024 && T * B <= kTwoStepMaxIds && TH <= 1024, "tile fits");
+  static_assert(LDS <= 160 * 1024 && TH <= 1024, "tile fits");
   // n: a length bound above the kernel's length, as for the staged kernels
-  KernelInfo k{A * B + 1, T, LM, SM, 0, TH, LDS, &launch_two_step<A, B, T, LM, SM>, 0, 0};
+  KernelInfo k{A * B + 1, T, LM, SM, 0, TH, LDS, &launch_two_step<A, B, T, LM, SM, 0>, 0, 0};
   k.mixed = mixed_variant(mixed_radix_code(A * B));
   k.two_step = A;
   k.fixed_n = A * B;
   return k;
+}
+
+// The same kernel as an FP32 pass of a power of two (roots table), with its
+// move-only form; registry.cpp says where it is taken and what it measured.
+template <int N, int T, int LM, int SM>
+void add_two_step_power(std::vector<KernelInfo>& v) {
+  constexpr int A = two_step_split(N), B = N / A;
+  KernelInfo k{N, T, LM, SM, 0, two_step_threads(B, T), T * two_step_stride(A, B) * 8,
+               &launch_two_step<A, B, T, LM, SM, kRoots>, 0, 0};
+  k.two_step = A;
+  k.r0 = A;
+  k.r1 = B;
+  k.r2 = 1;
+  v.push_back(k);
+  k.launch = &launch_two_step<A, B, T, LM, SM, kRoots | kMove>;
+  k.move_only = 1;
+  v.push_back(k);
+}
+template <int N, int T>
+void add_two_step_powers(std::vector<KernelInfo>& v) {
+  add_two_step_power<N, T, MODE_ROW, MODE_COL>(v);
+  add_two_step_power<N, T, MODE_ROW, MODE_ROW>(v);
+  add_two_step_power<N, T, MODE_COL, MODE_COL>(v);
 }
 
 // The kernels of the lengths LO <= n < HI that split, in tiles of 16 pencils

@@ -110,6 +110,29 @@ def test_cycled_order_of_other_lengths(shape):
         assert (got_in == place(order_in)).all() and (got_out == place(order_out)).all()
 
 
+def test_power_of_two_passes_in_two_steps():
+    """FP32 passes of 16..1024 points without a four-step twiddle: tiles by
+    length and pencils, the pass kernels where an option asks for their forms,
+    the halves kernels only where their tiles fill the CUs."""
+    def pick(shape, schedule="pencil", **kw):
+        return [(p["n"], p["tile"], bool(p["split"])) for p in
+                dft3d.describe(shape, schedule, **kw)["passes"]]
+    assert pick((64, 32, 16)) == [(16, 16, True), (32, 16, True), (64, 16, True)]
+    assert pick((256, 256, 256)) == [(256, 16, True)] * 3
+    assert pick((16, 256, 256)) == [(256, 8, True), (256, 8, True), (16, 16, True)]
+    assert pick((1024, 1024, 1024)) == [(1024, 16, True)] * 3
+    assert pick((256, 512, 512))[1] == (256, 32, True)             # cycled: axes 2, 0, 1
+    assert pick((64, 1024, 64), "slab")[0] == (64, 32, True)
+    assert pick((128, 512, 512))[1] == (128, 32, False)
+    assert pick((16, 512, 512), "slab")[2] == (16, 256, False)
+    assert pick((64, 32, 16), tile=64)[2] == (64, 64, False)
+    assert not any(s for _, _, s in pick((1024, 1024, 1024), nontemporal=1))
+    assert pick((1024, 16, 64), "slab")[-1] == (1024, 8, True)       # 32 halves tiles
+    assert pick((1024, 128, 64), "slab")[-1] == (1024, 32, False)    # 256 of them
+    assert pick((2048, 32, 32), "slab")[-1] == (2048, 4, False)
+    assert pick((2048, 64, 64), "slab")[-1] == (2048, 16, False)
+
+
 def bar(shape):
     return 1e-6 * sum(np.log2(n) + 1 for n in shape if n > 1) / 18.0
 
@@ -155,3 +178,23 @@ def test_auto_choices_of_other_lengths_on_the_gpu(shape):
     back = dft3d.ifftn(y) / x.size
     rt = (torch.linalg.vector_norm(back - xt) / torch.linalg.vector_norm(xt)).item()
     assert rt <= 2 * bar(shape)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,schedule", [((16, 32, 64), "slab"), ((64, 1024, 64), "slab"),
+                                            ((1024, 8, 256), "slab"), ((8, 512, 1024), "pencil"),
+                                            ((2048, 64, 4), "slab"), ((4, 32, 16), "pencil")])
+def test_power_of_two_passes_on_the_gpu(shape, schedule):
+    """Every tile of the power-of-two two-step passes and the forms that
+    replace the halves kernels on small grids, against the FP64 oracle."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("case two-step powers", shape, schedule, flush=True)
+    x = inputs.uniform_c64(shape, 63)
+    tol = 1e-6 * np.log2(x.size) / 18
+    for sign in (-1, 1):
+        y = dft3d.fftn(torch.from_numpy(x).cuda(), schedule=schedule, inverse=sign == 1)
+        torch.cuda.synchronize()
+        err = oracle.rel_l2(y.cpu().numpy(), oracle.dft3d(x.astype(np.complex128), sign, "fft"))
+        assert err <= tol, (shape, schedule, sign, err)
