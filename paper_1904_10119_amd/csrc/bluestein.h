@@ -126,9 +126,9 @@ constexpr int bluestein_lds_tables() {
 
 // BL: register blocking of the length-m FFTs (E elements per thread).
 template <int M, int T, class BL>
-__global__ void __launch_bounds__(T*(M / BL::E))
-bluestein_axis_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
-                      const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void bluestein_axis_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int E = BL::E;
   constexpr int P = M / E;
   constexpr int NST = num_stages<BL>();
@@ -207,6 +207,12 @@ bluestein_axis_kernel(const float2* src, float2* dst, const float2* __restrict__
 }
 
 template <int M, int T, class BL>
+__global__ void __launch_bounds__(T*(M / BL::E))
+bluestein_axis_kernel(const PassLaunch la) {
+  bluestein_axis_kernel_run<M, T, BL>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
+template <int M, int T, class BL>
 hipError_t launch_bluestein_axis(const PassArgs& a, const float2* src, float2* dst,
                                  const float2* tw, const float2* twp, hipStream_t stream) {
   constexpr int THREADS = T * (M / BL::E);
@@ -215,7 +221,7 @@ hipError_t launch_bluestein_axis(const PassArgs& a, const float2* src, float2* d
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.res_mask < 1 || 2 * a.res_mask - 1 > M) return hipErrorInvalidValue;
   hipLaunchKernelGGL((bluestein_axis_kernel<M, T, BL>), dim3((unsigned)blocks), dim3(THREADS),
-                     0, stream, src, dst, tw, twp, a);
+                     0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

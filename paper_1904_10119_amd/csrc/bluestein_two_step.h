@@ -77,9 +77,9 @@ constexpr int bluestein_two_step_threads(int a, int b, int t) {
 }
 
 template <int A, int B, int NMIN, int T, int LM>
-__global__ void __launch_bounds__(bluestein_two_step_threads(A, B, T))
-bluestein_two_step_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
-                          const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void bluestein_two_step_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int H = A / 2;
   constexpr int pitch = two_step_pitch(B), sq = two_step_stride(A, B);
   __shared__ float2 lds[T * sq];
@@ -179,6 +179,12 @@ bluestein_two_step_kernel(const float2* src, float2* dst, const float2* __restri
 }
 
 template <int A, int B, int NMIN, int T, int LM>
+__global__ void __launch_bounds__(bluestein_two_step_threads(A, B, T))
+bluestein_two_step_kernel(const PassLaunch la) {
+  bluestein_two_step_kernel_run<A, B, NMIN, T, LM>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
+template <int A, int B, int NMIN, int T, int LM>
 hipError_t launch_bluestein_two_step(const PassArgs& a, const float2* src, float2* dst,
                                      const float2* tw, const float2* twp, hipStream_t stream) {
   const int64_t blocks = (a.B + T - 1) / T;
@@ -186,7 +192,7 @@ hipError_t launch_bluestein_two_step(const PassArgs& a, const float2* src, float
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.res_mask < NMIN || 2 * a.res_mask > A * B || a.res_shift != A) return hipErrorInvalidValue;
   hipLaunchKernelGGL((bluestein_two_step_kernel<A, B, NMIN, T, LM>), dim3((unsigned)blocks),
-                     dim3(bluestein_two_step_threads(A, B, T)), 0, stream, src, dst, tw, twp, a);
+                     dim3(bluestein_two_step_threads(A, B, T)), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

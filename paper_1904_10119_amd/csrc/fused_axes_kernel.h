@@ -157,9 +157,9 @@ __device__ __forceinline__ void fused_stage2(const float2* lds, float2* dst,
 
 // One tile per workgroup.
 template <int A, int KC, int CONTIG, int SHUF>
-__global__ void __launch_bounds__(A* KC)
-fft_fused_axes_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
-                      const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_fused_axes_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   __shared__ float2 lds[A * fused_row<A, KC>()];
   __shared__ float2 twl[fused_tw_lds<A, KC, CONTIG, SHUF>()];
   const int tid = threadIdx.x;
@@ -175,15 +175,21 @@ fft_fused_axes_kernel(const float2* src, float2* dst, const float2* __restrict__
   fused_stage2<A, KC, CONTIG, SHUF>(lds, dst, tw, twp, a, ft, tid);
 }
 
+template <int A, int KC, int CONTIG, int SHUF>
+__global__ void __launch_bounds__(A* KC)
+fft_fused_axes_kernel(const PassLaunch la) {
+  fft_fused_axes_kernel_run<A, KC, CONTIG, SHUF>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
 // Persistent form: about one workgroup per CU walks the tiles w, w + G, ...
 // and loads the next tile's runs into registers as soon as the current
 // tile's first stage has left them, so the loads are in flight during the
 // second stage and the stores.  Past the last tile the prefetch re-reads
 // the last tile (in bounds).
 template <int A, int KC, int CONTIG, int SHUF>
-__global__ void __launch_bounds__(A* KC)
-fft_fused_axes_persistent(const float2* src, float2* dst, const float2* __restrict__ tw,
-                          const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_fused_axes_persistent_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   __shared__ float2 lds[A * fused_row<A, KC>()];
   __shared__ float2 twl[fused_tw_lds<A, KC, CONTIG, SHUF>()];
   const int tid = threadIdx.x;
@@ -210,12 +216,18 @@ fft_fused_axes_persistent(const float2* src, float2* dst, const float2* __restri
 }
 
 template <int A, int KC, int CONTIG, int SHUF>
+__global__ void __launch_bounds__(A* KC)
+fft_fused_axes_persistent(const PassLaunch la) {
+  fft_fused_axes_persistent_run<A, KC, CONTIG, SHUF>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
+template <int A, int KC, int CONTIG, int SHUF>
 hipError_t launch_fused_axes(const PassArgs& a, const float2* src, float2* dst,
                              const float2* tw, const float2* twp, hipStream_t stream) {
   if (a.B <= 0) return hipSuccess;
   if (a.B > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((fft_fused_axes_kernel<A, KC, CONTIG, SHUF>), dim3((unsigned)a.B),
-                     dim3(A * KC), 0, stream, src, dst, tw, twp, a);
+                     dim3(A * KC), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 
@@ -237,7 +249,7 @@ hipError_t launch_fused_axes_persistent(const PassArgs& a, const float2* src, fl
   int64_t grid = (int64_t)device_cu_count() * per_cu;
   if (grid > a.B) grid = a.B;
   hipLaunchKernelGGL((fft_fused_axes_persistent<A, KC, CONTIG, SHUF>), dim3((unsigned)grid),
-                     dim3(A * KC), 0, stream, src, dst, tw, twp, a);
+                     dim3(A * KC), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

@@ -158,9 +158,9 @@ __device__ __forceinline__ void halves_load(float2 (&lo)[32], float2 (&hi)[32], 
 // the whole tile is in registers before its first store, and tiles are
 // disjoint.
 template <int N, int T, int LM, int SM, int NT>
-__global__ void __launch_bounds__(T * (N / 64))
-fft_pass_halves(const float2* src, float2* dst, const float2* __restrict__ tw,
-                const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_pass_halves_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int SQ = lds_pencil_stride<N / 2, T>();
   __shared__ float2 lds[T * SQ];
   __shared__ float2 roots[N];
@@ -182,14 +182,20 @@ fft_pass_halves(const float2* src, float2* dst, const float2* __restrict__ tw,
   halves_half<N, T, LM, SM, NT, SQ, 1>(hi, lo, dst, roots, lds, a, tile, tid);
 }
 
+template <int N, int T, int LM, int SM, int NT>
+__global__ void __launch_bounds__(T * (N / 64))
+fft_pass_halves(const PassLaunch la) {
+  fft_pass_halves_run<N, T, LM, SM, NT>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
 // Persistent form: about one resident workgroup per CU walks the tiles
 // (w, w + G, ...); once the first half is stored and the second parked in
 // LDS, both halves of the next tile are loaded into the freed registers
 // while the second half goes through its stages.
 template <int N, int T, int LM, int SM, int NT>
-__global__ void __launch_bounds__(T * (N / 64))
-fft_pass_halves_persistent(const float2* src, float2* dst, const float2* __restrict__ tw,
-                           const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_pass_halves_persistent_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int SQ = lds_pencil_stride<N / 2, T>();
   __shared__ float2 lds[T * SQ];
   __shared__ float2 roots[N];
@@ -226,6 +232,12 @@ fft_pass_halves_persistent(const float2* src, float2* dst, const float2* __restr
 }
 
 template <int N, int T, int LM, int SM, int NT>
+__global__ void __launch_bounds__(T * (N / 64))
+fft_pass_halves_persistent(const PassLaunch la) {
+  fft_pass_halves_persistent_run<N, T, LM, SM, NT>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
+template <int N, int T, int LM, int SM, int NT>
 hipError_t launch_halves_persistent(const PassArgs& a, const float2* src, float2* dst,
                                     const float2* tw, const float2* twp, hipStream_t stream) {
   const int64_t tiles = (a.B + T - 1) / T;
@@ -241,7 +253,7 @@ hipError_t launch_halves_persistent(const PassArgs& a, const float2* src, float2
   int64_t grid = (int64_t)device_cu_count() * per_cu;
   if (grid > tiles) grid = tiles;
   hipLaunchKernelGGL((fft_pass_halves_persistent<N, T, LM, SM, NT>), dim3((unsigned)grid),
-                     dim3(T * (N / 64)), 0, stream, src, dst, tw, twp, a);
+                     dim3(T * (N / 64)), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 
@@ -252,7 +264,7 @@ hipError_t launch_halves(const PassArgs& a, const float2* src, float2* dst, cons
   if (tiles <= 0) return hipSuccess;
   if (tiles > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((fft_pass_halves<N, T, LM, SM, NT>), dim3((unsigned)tiles),
-                     dim3(T * (N / 64)), 0, stream, src, dst, tw, twp, a);
+                     dim3(T * (N / 64)), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

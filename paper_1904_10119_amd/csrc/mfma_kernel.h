@@ -596,10 +596,10 @@ template <int N, int TE = mfma_tile_elems<N>()> constexpr int mfma_one_tile_wave
 
 // One tile per workgroup (TE tile elements: the default, or twice that in
 // the wide form, whose rotated store writes rows of twice the pencils).
-template <int N, int LM, int SM, int PREC, int L, int TE = mfma_tile_elems<N>()>
-__global__ void __launch_bounds__((mfma_threads<N, TE>()), (mfma_one_tile_waves<N, TE>()))
-fft_pass_mfma(const float2* src, float2* dst, const float2* __restrict__ tw,
-              const unsigned short* __restrict__ leaf, const PassArgs a) {
+template <int N, int LM, int SM, int PREC, int L, int TE>
+__device__ __forceinline__ void fft_pass_mfma_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const unsigned short* __restrict__ leaf, const PassArgs& a) {
   __shared__ float2 buf[mfma_buf_elems<N, TE>()];
   __shared__ float2 ltw[N];
   const int tid = threadIdx.x;
@@ -616,14 +616,21 @@ fft_pass_mfma(const float2* src, float2* dst, const float2* __restrict__ tw,
   mfma_finish<N, SM, L, TE>(buf, dst, ltw, a, tile, tid);
 }
 
+template <int N, int LM, int SM, int PREC, int L, int TE = mfma_tile_elems<N>()>
+__global__ void __launch_bounds__((mfma_threads<N, TE>()), (mfma_one_tile_waves<N, TE>()))
+fft_pass_mfma(const PassLaunch la) {
+  fft_pass_mfma_run<N, LM, SM, PREC, L, TE>(
+      la.src, la.dst, la.tw, reinterpret_cast<const unsigned short*>(la.twp), la.a);
+}
+
 // Persistent form: about one resident workgroup per CU walks the tiles
 // (w, w + G, ...; remapped per XCD).  As soon as the first stage has
 // consumed the registers, the next tile's loads go out, so they are in
 // flight during the remaining stages and the stores.
 template <int N, int LM, int SM, int PREC, int L>
-__global__ void __launch_bounds__(mfma_threads<N>())
-fft_pass_mfma_persistent(const float2* src, float2* dst, const float2* __restrict__ tw,
-                         const unsigned short* __restrict__ leaf, const PassArgs a) {
+__device__ __forceinline__ void fft_pass_mfma_persistent_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const unsigned short* __restrict__ leaf, const PassArgs& a) {
   constexpr int T = mfma_tile_elems<N>() / N;
   __shared__ float2 buf[2][mfma_buf_elems<N>()];
   __shared__ float2 ltw[N];
@@ -654,6 +661,13 @@ fft_pass_mfma_persistent(const float2* src, float2* dst, const float2* __restric
   }
 }
 
+template <int N, int LM, int SM, int PREC, int L>
+__global__ void __launch_bounds__(mfma_threads<N>())
+fft_pass_mfma_persistent(const PassLaunch la) {
+  fft_pass_mfma_persistent_run<N, LM, SM, PREC, L>(
+      la.src, la.dst, la.tw, reinterpret_cast<const unsigned short*>(la.twp), la.a);
+}
+
 template <int N, int LM, int SM, int PREC, int L, int TE = mfma_tile_elems<N>()>
 hipError_t launch_mfma(const PassArgs& a, const float2* src, float2* dst, const float2* tw,
                        const float2* leaf, hipStream_t stream) {
@@ -662,8 +676,7 @@ hipError_t launch_mfma(const PassArgs& a, const float2* src, float2* dst, const 
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((fft_pass_mfma<N, LM, SM, PREC, L, TE>), dim3((unsigned)blocks),
-                     dim3(mfma_threads<N, TE>()), 0, stream, src, dst, tw,
-                     reinterpret_cast<const unsigned short*>(leaf), a);
+                     dim3(mfma_threads<N, TE>()), 0, stream, PassLaunch{src, dst, tw, leaf, a});
   return hipGetLastError();
 }
 
@@ -685,8 +698,7 @@ hipError_t launch_mfma_persistent(const PassArgs& a, const float2* src, float2* 
   int64_t grid = (int64_t)device_cu_count() * per_cu;
   if (grid > tiles) grid = tiles;
   hipLaunchKernelGGL((fft_pass_mfma_persistent<N, LM, SM, PREC, L>), dim3((unsigned)grid),
-                     dim3(mfma_threads<N>()), 0, stream, src, dst, tw,
-                     reinterpret_cast<const unsigned short*>(leaf), a);
+                     dim3(mfma_threads<N>()), 0, stream, PassLaunch{src, dst, tw, leaf, a});
   return hipGetLastError();
 }
 

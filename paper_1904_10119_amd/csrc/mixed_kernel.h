@@ -344,10 +344,10 @@ __device__ __forceinline__ void mixed_rest(uint64_t code, int ns, float2* buf, f
 // contiguous, the pencil's points at stride ijs) first copy the tile into
 // LDS with lanes across the pencils (thread on pencil tid mod T), then run
 // the first stage from there.
-template <int T, int NMAX, int TH, int VAR, int LM = MODE_ROW, int SM = MODE_COL>
-__global__ void __launch_bounds__(TH)
-fft_mixed_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
-                 const float2* __restrict__ twp, const PassArgs a) {
+template <int T, int NMAX, int TH, int VAR, int LM, int SM>
+__device__ __forceinline__ void fft_mixed_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int P = TH / T;             // threads per pencil
   constexpr int V = NMAX / P;           // points per thread
   constexpr bool COMP = VAR == 1 && NMAX <= 2048;  // radices 10 and 16
@@ -412,6 +412,12 @@ fft_mixed_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
   mixed_rest<T, NMAX, TH, VAR, SM>(code, ns, buf, pen, twv, dst, a, tile, n, sq, tid, p);
 }
 
+template <int T, int NMAX, int TH, int VAR, int LM = MODE_ROW, int SM = MODE_COL>
+__global__ void __launch_bounds__(TH)
+fft_mixed_kernel(const PassLaunch la) {
+  fft_mixed_kernel_run<T, NMAX, TH, VAR, LM, SM>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
 // Stages of a compile-time radix code (the first stage done, NS = its radix).
 template <uint64_t CODE, int NS, int V, int N>
 __device__ __forceinline__ void mixed_stages_fixed(float2* pen, const float2* twv, int p,
@@ -427,9 +433,9 @@ __device__ __forceinline__ void mixed_stages_fixed(float2* pen, const float2* tw
 // CODE (variant 1 radices): the stage sizes, the butterfly index arithmetic
 // and the LDS offsets fold into constants and the radix switch disappears.
 template <int T, int NMAX, int TH, int N, uint64_t CODE>
-__global__ void __launch_bounds__(TH)
-fft_mixed_fixed(const float2* src, float2* dst, const float2* __restrict__ tw,
-                const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_mixed_fixed_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int P = TH / T;
   constexpr int V = NMAX / P;
   constexpr bool TWL = 2 * (T * NMAX + NMAX) * 8 <= 160 * 1024;
@@ -459,6 +465,12 @@ fft_mixed_fixed(const float2* src, float2* dst, const float2* __restrict__ tw,
 }
 
 template <int T, int NMAX, int TH, int N, uint64_t CODE>
+__global__ void __launch_bounds__(TH)
+fft_mixed_fixed(const PassLaunch la) {
+  fft_mixed_fixed_run<T, NMAX, TH, N, CODE>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
+template <int T, int NMAX, int TH, int N, uint64_t CODE>
 hipError_t launch_mixed_fixed(const PassArgs& a, const float2* src, float2* dst,
                               const float2* tw, const float2* twp, hipStream_t stream) {
   const int64_t blocks = (a.B + T - 1) / T;
@@ -466,7 +478,7 @@ hipError_t launch_mixed_fixed(const PassArgs& a, const float2* src, float2* dst,
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.res_mask != N || (uint64_t)a.twp_mask != CODE) return hipErrorInvalidValue;
   hipLaunchKernelGGL((fft_mixed_fixed<T, NMAX, TH, N, CODE>), dim3((unsigned)blocks), dim3(TH),
-                     0, stream, src, dst, tw, twp, a);
+                     0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 
@@ -494,7 +506,7 @@ hipError_t launch_mixed(const PassArgs& a, const float2* src, float2* dst, const
   if (a.res_mask < 2 || a.res_mask >= NMAX || !mixed_kernel_runs(VAR, NMAX, (uint64_t)a.twp_mask))
     return hipErrorInvalidValue;  // a stage radix this kernel does not run
   hipLaunchKernelGGL((fft_mixed_kernel<T, NMAX, TH, VAR, LM, SM>), dim3((unsigned)blocks),
-                     dim3(TH), 0, stream, src, dst, tw, twp, a);
+                     dim3(TH), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

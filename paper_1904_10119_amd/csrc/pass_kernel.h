@@ -236,9 +236,9 @@ __device__ __forceinline__ void transform_store_tile(float2 (&v)[E], float2* dst
 
 // One workgroup per tile.
 template <int N, int T, int LM, int SM, int TW, int NT>
-__global__ void __launch_bounds__(T*(N / Blocking<N>::E))
-fft_pass_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
-                const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_pass_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   // src and dst may be the same buffer (in-place passes): every element of a
   // tile is read before any element of it is written, and tiles are disjoint.
   using BL = Blocking<N>;
@@ -259,6 +259,12 @@ fft_pass_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
                                                            tid, q, p);
 }
 
+template <int N, int T, int LM, int SM, int TW, int NT>
+__global__ void __launch_bounds__(T*(N / Blocking<N>::E))
+fft_pass_kernel(const PassLaunch la) {
+  fft_pass_kernel_run<N, T, LM, SM, TW, NT>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
 // Persistent form: a grid of about one resident workgroup per CU walks the
 // tiles (virtual tile w, w + G, w + 2G, ... for workgroup w, remapped so
 // that each XCD takes a contiguous range) and loads tile i+1 into registers
@@ -266,9 +272,9 @@ fft_pass_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
 // for a workgroup to finish its arithmetic.  The stage twiddles are copied
 // to LDS once, keeping their reads off the vector-memory queue.
 template <int N, int T, int LM, int SM, int TW, int NT, class BL>
-__global__ void __launch_bounds__(T*(N / BL::E))
-fft_pass_persistent(const float2* src, float2* dst, const float2* __restrict__ tw,
-                    const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_pass_persistent_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int E = BL::E;
   constexpr int P = N / E;
   constexpr int NTHR = T * P;
@@ -320,6 +326,12 @@ fft_pass_persistent(const float2* src, float2* dst, const float2* __restrict__ t
   }
 }
 
+template <int N, int T, int LM, int SM, int TW, int NT, class BL>
+__global__ void __launch_bounds__(T*(N / BL::E))
+fft_pass_persistent(const PassLaunch la) {
+  fft_pass_persistent_run<N, T, LM, SM, TW, NT, BL>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
 template <int N, int T, int LM, int SM, int TW, int NT>
 hipError_t launch_pass(const PassArgs& a, const float2* src, float2* dst,
                        const float2* tw, const float2* twp, hipStream_t stream) {
@@ -328,7 +340,7 @@ hipError_t launch_pass(const PassArgs& a, const float2* src, float2* dst,
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((fft_pass_kernel<N, T, LM, SM, TW, NT>), dim3((unsigned)blocks),
-                     dim3(THREADS), 0, stream, src, dst, tw, twp, a);
+                     dim3(THREADS), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 
@@ -351,7 +363,7 @@ hipError_t launch_persistent(const PassArgs& a, const float2* src, float2* dst,
   int64_t grid = (int64_t)device_cu_count() * per_cu;
   if (grid > tiles) grid = tiles;
   hipLaunchKernelGGL((fft_pass_persistent<N, T, LM, SM, TW, NT, BL>), dim3((unsigned)grid),
-                     dim3(THREADS), 0, stream, src, dst, tw, twp, a);
+                     dim3(THREADS), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

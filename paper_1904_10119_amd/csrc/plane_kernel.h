@@ -104,12 +104,18 @@ __device__ __forceinline__ void plane_run(const float2* src, float2* dst,
 }
 
 template <int N1, int N2>
-__global__ void __launch_bounds__((N1 * N2 / plane_elems<N1, N2>()))
-fft_plane_kernel(const float2* src, float2* dst, const float2* __restrict__ tw2,
-                 const float2* __restrict__ tw1, const PassArgs a) {
+__device__ __forceinline__ void fft_plane_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw2,
+    const float2* __restrict__ tw1, const PassArgs& a) {
   __shared__ float2 lds[plane_lds_elems<N1, N2>()];
   plane_run<N1, N2, plane_elems<N1, N2>()>(src, dst, tw2, tw1, a, blockIdx.x, lds,
                                            threadIdx.x);
+}
+
+template <int N1, int N2>
+__global__ void __launch_bounds__((N1 * N2 / plane_elems<N1, N2>()))
+fft_plane_kernel(const PassLaunch la) {
+  fft_plane_kernel_run<N1, N2>(la.src, la.dst, la.tw, la.twp, la.a);
 }
 
 template <int N1, int N2>
@@ -118,7 +124,7 @@ hipError_t launch_plane(const PassArgs& a, const float2* src, float2* dst, const
   if (a.B <= 0) return hipSuccess;
   if (a.B > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((fft_plane_kernel<N1, N2>), dim3((unsigned)a.B),
-                     dim3(N1 * N2 / plane_elems<N1, N2>()), 0, stream, src, dst, tw, twp, a);
+                     dim3(N1 * N2 / plane_elems<N1, N2>()), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

@@ -43,9 +43,9 @@ template <int T, int NMAX> constexpr bool rader_twiddles_in_lds() {
 }
 
 template <int T, int NMAX, int TH, int VAR>
-__global__ void __launch_bounds__(TH)
-rader_axis_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
-                  const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void rader_axis_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int P = TH / T;   // threads per pencil
   constexpr int V = NMAX / P; // points per thread
   constexpr bool COMP = VAR == 1 && NMAX <= 2048;
@@ -186,14 +186,20 @@ rader_axis_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
   }
 }
 
+template <int T, int NMAX, int TH, int VAR>
+__global__ void __launch_bounds__(TH)
+rader_axis_kernel(const PassLaunch la) {
+  rader_axis_kernel_run<T, NMAX, TH, VAR>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
 // The same pass for one prime N known at compile time, CODE the radix code
 // of N - 1 (variant 1 radices): stage sizes and offsets fold into constants
 // and the radix switch disappears, which keeps the kernel's registers low
 // enough for two workgroups per CU.
 template <int T, int NMAX, int TH, int N, uint64_t CODE>
-__global__ void __launch_bounds__(TH)
-rader_axis_fixed(const float2* src, float2* dst, const float2* __restrict__ tw,
-                 const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void rader_axis_fixed_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   constexpr int P = TH / T;
   constexpr int V = NMAX / P;
   constexpr int L = N - 1;
@@ -310,6 +316,12 @@ rader_axis_fixed(const float2* src, float2* dst, const float2* __restrict__ tw,
 }
 
 template <int T, int NMAX, int TH, int N, uint64_t CODE>
+__global__ void __launch_bounds__(TH)
+rader_axis_fixed(const PassLaunch la) {
+  rader_axis_fixed_run<T, NMAX, TH, N, CODE>(la.src, la.dst, la.tw, la.twp, la.a);
+}
+
+template <int T, int NMAX, int TH, int N, uint64_t CODE>
 hipError_t launch_rader_fixed(const PassArgs& a, const float2* src, float2* dst,
                               const float2* tw, const float2* twp, hipStream_t stream) {
   const int64_t blocks = (a.B + T - 1) / T;
@@ -317,7 +329,7 @@ hipError_t launch_rader_fixed(const PassArgs& a, const float2* src, float2* dst,
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.res_mask != N || (uint64_t)a.twp_mask != CODE) return hipErrorInvalidValue;
   hipLaunchKernelGGL((rader_axis_fixed<T, NMAX, TH, N, CODE>), dim3((unsigned)blocks), dim3(TH),
-                     0, stream, src, dst, tw, twp, a);
+                     0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 
@@ -344,7 +356,7 @@ hipError_t launch_rader(const PassArgs& a, const float2* src, float2* dst, const
       !mixed_kernel_runs(VAR, NMAX, (uint64_t)a.twp_mask))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL((rader_axis_kernel<T, NMAX, TH, VAR>), dim3((unsigned)blocks), dim3(TH), 0,
-                     stream, src, dst, tw, twp, a);
+                     stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 

@@ -205,30 +205,29 @@ void make_chirp(int64_t n, float2* out) {
 }
 
 void make_bluestein_filter(int64_t n, int64_t m, int a, float2* out) {
-  // wrapped filter h[d] = conj(w[|d|]) at d mod m, in FP64
-  std::vector<double> hr(m, 0.0), hi(m, 0.0);
-  for (int64_t d = 0; d < n; ++d) {
-    double c, s;
-    root_fp64((d * d) % (2 * n), 2 * n, c, s);  // w[d] = c - i s, conj = c + i s
-    hr[d] = c;
-    hi[d] = s;
-    if (d > 0) {
-      hr[m - d] = c;
-      hi[m - d] = s;
-    }
-  }
-  std::vector<double> rc(m), rs(m);
+  // wrapped filter h[d] = conj(w[|d|]) at d mod m; h[m - d] = h[d], so
+  // H[l] = h[0] + 2 sum_{0 < d < n} h[d] cos(2 pi d l / m) and H[m - l] = H[l]
+  std::vector<double> hr(n), hi(n), rc(m), rs(m);
+  for (int64_t d = 0; d < n; ++d)
+    root_fp64((d * d) % (2 * n), 2 * n, hr[d], hi[d]);  // w[d] = c - i s, conj = c + i s
   for (int64_t l = 0; l < m; ++l) root_fp64(l, m, rc[l], rs[l]);
-  for (int64_t l = 0; l < m; ++l) {
-    double yr = 0.0, yi = 0.0;
-    for (int64_t d = 0; d < m; ++d) {
-      if (hr[d] == 0.0 && hi[d] == 0.0) continue;
-      const int64_t e = (d * l) % m;  // exp(-2 pi i d l / m) = rc - i rs
-      yr += hr[d] * rc[e] + hi[d] * rs[e];
-      yi += hi[d] * rc[e] - hr[d] * rs[e];
-    }
+  auto put = [&](int64_t l, double yr, double yi) {
     const int64_t at = a ? l % a * (m / a) + l / a : l;
     out[at] = make_float2((float)(yr / (double)m), (float)(yi / (double)m));
+  };
+  for (int64_t l = 0; l <= m / 2; ++l) {
+    double yr = 0.0, yi = 0.0;
+    int64_t e = 0;  // d l mod m
+    for (int64_t d = 1; d < n; ++d) {
+      e += l;
+      if (e >= m) e -= m;
+      yr += hr[d] * rc[e];
+      yi += hi[d] * rc[e];
+    }
+    yr = hr[0] + 2.0 * yr;
+    yi = hi[0] + 2.0 * yi;
+    put(l, yr, yi);
+    if (l > 0 && l < m - l) put(m - l, yr, yi);
   }
 }
 

@@ -136,14 +136,20 @@ __device__ __forceinline__ void two_step_second(float2* dst, const float2* __res
 // orders are compile-time constants (sizes and LDS offsets fold, no radix
 // switch, and each length has its own register count).
 template <int A, int B, int T, int TH, int LM, int SM, int FORM>
-__global__ void __launch_bounds__(TH)
-fft_two_step_kernel(const float2* src, float2* dst, const float2* __restrict__ tw,
-                   const float2* __restrict__ twp, const PassArgs a) {
+__device__ __forceinline__ void fft_two_step_kernel_run(
+    const float2* src, float2* dst, const float2* __restrict__ tw,
+    const float2* __restrict__ twp, const PassArgs& a) {
   __shared__ float2 lds[T * two_step_stride(A, B)];
   const int tid = threadIdx.x;
   const int64_t tile = tile_index(blockIdx.x, gridDim.x, a.xcd_remap);
   two_step_first<A, B, T, LM, FORM>(src, a, tile, lds, tid);
   two_step_second<A, B, T, SM, FORM>(dst, tw, a, tile, lds, tid);
+}
+
+template <int A, int B, int T, int TH, int LM, int SM, int FORM>
+__global__ void __launch_bounds__(TH)
+fft_two_step_kernel(const PassLaunch la) {
+  fft_two_step_kernel_run<A, B, T, TH, LM, SM, FORM>(la.src, la.dst, la.tw, la.twp, la.a);
 }
 
 // Threads of a two-step workgroup: a butterfly of step 1 for each (at most
@@ -159,7 +165,7 @@ hipError_t launch_two_step(const PassArgs& a, const float2* src, float2* dst, co
   if (FORM == 0 && (a.res_shift != A || a.res_mask != A * B)) return hipErrorInvalidValue;
   constexpr int TH = two_step_threads(B, T);
   hipLaunchKernelGGL((fft_two_step_kernel<A, B, T, TH, LM, SM, FORM>), dim3((unsigned)blocks),
-                     dim3(TH), 0, stream, src, dst, tw, twp, a);
+                     dim3(TH), 0, stream, PassLaunch{src, dst, tw, twp, a});
   return hipGetLastError();
 }
 
