@@ -90,6 +90,30 @@ def lib():
     return L
 
 
+# torch's complex64, and its call for the raw handle of a device's current
+# stream (0.1 us, where torch.cuda.current_stream(device).cuda_stream takes
+# 1.9: a transform of 32^3 points is launched in 7.5); set on first use.
+_complex64 = None
+_current_raw_stream = None
+
+
+def _load_torch() -> None:
+    global _complex64, _current_raw_stream
+    import torch
+    _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _complex64 = torch.complex64
+
+
+def _raw_stream(device) -> int:
+    """The current stream of a CUDA tensor's device."""
+    if _complex64 is None:
+        _load_torch()
+    if _current_raw_stream is not None:
+        return _current_raw_stream(device.index)
+    import torch
+    return torch.cuda.current_stream(device).cuda_stream
+
+
 def _check(st: int, what: str) -> None:
     if st != OK:
         raise Dft3dError(st, what)
@@ -179,6 +203,7 @@ class Plan:
                             ctypes.byref(h)), "dft3d_plan")
         self._h = h
         self._ws = None
+        self._need = None  # workspace bytes of the current options, once asked for
         try:
             if precision != "fp32":
                 self.set_option(OPT_PRECISION, PRECISIONS[precision])
@@ -223,6 +248,7 @@ class Plan:
         return self._h
 
     def set_option(self, key: int, value: int) -> None:
+        self._need = None
         _check(lib().dft3d_plan_set_option(self._h, key, int(value)), "set_option")
 
     def get_option(self, key: int) -> int:
@@ -242,39 +268,55 @@ class Plan:
 
     def bind_workspace(self, device) -> None:
         import torch
-        need = self.workspace_size()
+        need = self._need = self.workspace_size()
         if need == 0 or (self._ws is not None and self._ws.numel() >= need):
             return
         self._ws = torch.empty(need, dtype=torch.uint8, device=device)
         _check(lib().dft3d_set_workspace(self._h, self._ws.data_ptr(), need),
                "set_workspace")
 
+    def _check_tensors(self, x, out) -> None:
+        for t in (x, out):
+            if t.dtype is not _complex64 or not t.is_cuda or not t.is_contiguous():
+                raise ValueError("expected contiguous complex64 CUDA tensors")
+            if t.shape != self.shape:
+                raise ValueError(f"shape {tuple(t.shape)} != plan {self.shape}")
+
+    def _bound(self) -> bool:
+        """Whether a workspace large enough for the plan's options is bound.  An
+        option set through the C ABI behind this object either shows up as
+        ERR_WORKSPACE_TOO_SMALL, before anything is enqueued, or, for a plan
+        that needed none, makes the library allocate the plan's own."""
+        need = self._need
+        return need is not None and (need == 0 or (self._ws is not None
+                                                   and self._ws.numel() >= need))
+
     def execute(self, x, out, inverse: bool = False, stream=None) -> None:
         """x, out: contiguous complex64 CUDA tensors of the plan's shape."""
-        import torch
-        for t in (x, out):
-            if t.dtype != torch.complex64 or not t.is_cuda or not t.is_contiguous():
-                raise ValueError("expected contiguous complex64 CUDA tensors")
-            if tuple(t.shape) != self.shape:
-                raise ValueError(f"shape {tuple(t.shape)} != plan {self.shape}")
-        self.bind_workspace(x.device)
-        s = stream if stream is not None else torch.cuda.current_stream(x.device)
-        _check(lib().dft3d_execute(self._h, x.data_ptr(), out.data_ptr(),
-                                   1 if inverse else -1, s.cuda_stream),
-               "dft3d_execute")
+        L = _lib or lib()
+        if _complex64 is None:
+            _load_torch()
+        self._check_tensors(x, out)
+        if not self._bound():
+            self.bind_workspace(x.device)
+        s = _raw_stream(x.device) if stream is None else stream.cuda_stream
+        st = L.dft3d_execute(self._h, x.data_ptr(), out.data_ptr(), 1 if inverse else -1, s)
+        if st == ERR_WORKSPACE_TOO_SMALL:
+            self.bind_workspace(x.device)
+            st = L.dft3d_execute(self._h, x.data_ptr(), out.data_ptr(), 1 if inverse else -1, s)
+        if st != OK:
+            raise Dft3dError(st, "dft3d_execute")
 
     def execute_noalloc(self, x, out, inverse: bool = False, stream=None) -> None:
         """As execute(), through dft3d_execute_noalloc: the workspace is the
         library's static per-device array (nothing is allocated)."""
-        import torch
-        for t in (x, out):
-            if t.dtype != torch.complex64 or not t.is_cuda or not t.is_contiguous():
-                raise ValueError("expected contiguous complex64 CUDA tensors")
-            if tuple(t.shape) != self.shape:
-                raise ValueError(f"shape {tuple(t.shape)} != plan {self.shape}")
-        s = stream if stream is not None else torch.cuda.current_stream(x.device)
-        _check(lib().dft3d_execute_noalloc(self._h, x.data_ptr(), out.data_ptr(),
-                                           1 if inverse else -1, s.cuda_stream),
+        L = _lib or lib()
+        if _complex64 is None:
+            _load_torch()
+        self._check_tensors(x, out)
+        s = _raw_stream(x.device) if stream is None else stream.cuda_stream
+        _check(L.dft3d_execute_noalloc(self._h, x.data_ptr(), out.data_ptr(),
+                                       1 if inverse else -1, s),
                "dft3d_execute_noalloc")
 
     def close(self) -> None:
@@ -296,8 +338,8 @@ _plans: Dict[Tuple, Plan] = {}
 def get_plan(shape, schedule="auto", precision="fp32", device_index=0, **opts) -> Plan:
     if "radices" in opts:
         opts["radices"] = radix_code(opts["radices"])
-    key = (tuple(int(s) for s in shape), schedule, precision, device_index,
-           tuple(sorted(opts.items())))
+    key = (tuple(shape), schedule, precision, device_index,
+           tuple(sorted(opts.items())) if opts else ())
     p = _plans.get(key)
     if p is None:
         p = Plan(shape, schedule, precision=precision, **opts)
@@ -375,12 +417,13 @@ def fftn_batched(xs: List, inverse: bool = False, outs: Optional[List] = None,
     plans = [get_plan(x.shape, schedule, "fp32", x.device.index or 0,
                       **({"batch_launch": bl} if bl else {})) for x in xs]
     for p, x in zip(plans, xs):
-        p.bind_workspace(x.device)
+        if not p._bound():
+            p.bind_workspace(x.device)
     arr = ctypes.c_void_p * max(n, 1)
-    hp = arr(*[p.handle.value for p in plans])
+    hp = arr(*[p._h.value for p in plans])
     ip = arr(*[x.data_ptr() for x in xs])
     op = arr(*[o.data_ptr() for o in outs])
-    s = torch.cuda.current_stream(xs[0].device) if n else torch.cuda.current_stream()
-    _check(lib().dft3d_execute_batched(hp, ip, op, n, 1 if inverse else -1,
-                                       s.cuda_stream), "dft3d_execute_batched")
+    s = _raw_stream(xs[0].device) if n else torch.cuda.current_stream().cuda_stream
+    _check(lib().dft3d_execute_batched(hp, ip, op, n, 1 if inverse else -1, s),
+           "dft3d_execute_batched")
     return outs
