@@ -159,6 +159,7 @@ struct BatchGraph {
   std::vector<int> item_plan, item_pass;
   std::vector<Level> levels;
   BatchItem* staging = nullptr;       // pinned host copy of the descriptors
+  void* staging_dev = nullptr;        // and its device address
   BatchItem* d_items = nullptr;
   // Workspaces of problems that cannot use their plan's own: a plan that
   // appears more than once, or whose bound workspace overlaps the workspace
@@ -312,6 +313,7 @@ int build_batch(BatchGraph* g, dft3d_plan_s* const* plans, int count, bool persi
   if (hipGetDevice(&g->device) != hipSuccess) return DFT3D_ERR_HIP;
   if (hipHostMalloc(reinterpret_cast<void**>(&g->staging), bytes, hipHostMallocDefault) !=
           hipSuccess ||
+      hipHostGetDevicePointer(&g->staging_dev, g->staging, 0) != hipSuccess ||
       hipMalloc(&g->d_items, bytes) != hipSuccess) {
     (void)hipGetLastError();
     return DFT3D_ERR_OUT_OF_MEMORY;
@@ -546,10 +548,12 @@ int batch_execute(dft3d_plan_s* const* given, const void* const* in, void* const
   }
   if (!g->persistent) {
     if (!ready) {
-      const size_t bytes = sizeof(BatchItem) * g->items.size();
-      if (hipMemcpyAsync(g->d_items, g->staging, bytes, hipMemcpyHostToDevice, stream) !=
-              hipSuccess ||
-          hipEventRecord(g->copied, stream) != hipSuccess)
+      static_assert(sizeof(BatchItem) % 8 == 0, "whole words");
+      const int words = (int)(sizeof(BatchItem) / 8 * g->items.size());
+      hipLaunchKernelGGL(batch_upload_kernel, dim3((words + 255) / 256), dim3(256), 0, stream,
+                         reinterpret_cast<const unsigned long long*>(g->staging_dev),
+                         reinterpret_cast<unsigned long long*>(g->d_items), words);
+      if (hipGetLastError() != hipSuccess || hipEventRecord(g->copied, stream) != hipSuccess)
         return DFT3D_ERR_HIP;
       g->launched = true;
       g->last = cur;
