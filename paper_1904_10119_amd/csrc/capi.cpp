@@ -62,7 +62,8 @@ void free_workspace(dft3d_plan_s* p) {
 // (length, A, radix code).
 using MixedKey = std::tuple<int64_t, int, uint64_t>;
 MixedKey mixed_key(const Pass& ps) {
-  if (ps.k->rader) return {ps.rader_n - 1, 0, (uint64_t)ps.args.twp_mask};
+  if (ps.k->rader)
+    return {ps.rader_n - 1, ps.k->two_step, ps.k->two_step ? 0 : (uint64_t)ps.args.twp_mask};
   if (ps.k->bluestein) return {ps.k->n, ps.k->two_step, 0};
   if (ps.k->two_step) return {ps.args.res_mask, ps.args.res_shift, 0};
   return {ps.args.res_mask, 0, (uint64_t)ps.args.twp_mask};
@@ -95,8 +96,8 @@ int rebuild(dft3d_plan_s* p) {
   // mixed-radix twiddles (value: offset): staged passes per length n and
   // radix code (n, 0, code), two-step passes per length and split (n, A, 0)
   std::map<MixedKey, int64_t> mx_offsets;
-  // Rader tables per prime length n (value: offset)
-  std::map<int64_t, int64_t> rd_offsets;
+  // Rader tables per prime length n and first step A (0: staged)
+  std::map<std::pair<int64_t, int>, int64_t> rd_offsets;
   int64_t total = 0;
   std::vector<const Pass*> all;
   for (const Pass& ps : passes) all.push_back(&ps);
@@ -115,8 +116,8 @@ int rebuild(dft3d_plan_s* p) {
         mx_offsets[key] = total;
         total += std::get<0>(key);
       }
-      if (!rd_offsets.count(ps.rader_n)) {
-        rd_offsets[ps.rader_n] = total;
+      if (!rd_offsets.count({ps.rader_n, ps.k->two_step})) {
+        rd_offsets[{ps.rader_n, ps.k->two_step}] = total;
         total += rader_table_size(ps.rader_n);
       }
       continue;
@@ -162,7 +163,8 @@ int rebuild(dft3d_plan_s* p) {
     else
       make_mixed_twiddles(len, std::get<2>(kv.first), host.data() + kv.second);
   }
-  for (auto& kv : rd_offsets) make_rader_tables(kv.first, host.data() + kv.second);
+  for (auto& kv : rd_offsets)
+    make_rader_tables(kv.first.first, kv.first.second, host.data() + kv.second);
   for (auto& kv : bl_offsets) {
     const int64_t n = kv.first.first;
     const KernelInfo* k = kv.first.second;
@@ -193,7 +195,7 @@ int rebuild(dft3d_plan_s* p) {
     for (const Pass& ps : list) {
       if (ps.k->rader) {
         tw.push_back(mx_offsets[mixed_key(ps)]);
-        twp.push_back(rd_offsets[ps.rader_n]);
+        twp.push_back(rd_offsets[{ps.rader_n, ps.k->two_step}]);
         continue;
       }
       if (ps.k->mixed) {  // the stage twiddles of the length

@@ -153,7 +153,8 @@ const KernelInfo* find_rader_kernel(int64_t n, int tile);
 // w_n^(g^-m), FP64-built (n - 1 entries), then the generator powers g^j mod
 // n (n - 1 32-bit integers, packed two per float2): rader_table_size slots.
 int64_t rader_table_size(int64_t n);
-void make_rader_tables(int64_t n, float2* out);
+// a > 0: the first table in the order of a two-step kernel of first step a.
+void make_rader_tables(int64_t n, int a, float2* out);
 // The one-pass Bluestein axis kernel of convolution length m with the given
 // tile, else the length's default tile; null if none is compiled.
 const KernelInfo* find_bluestein_kernel(int m, int tile);

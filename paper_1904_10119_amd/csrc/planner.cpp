@@ -323,6 +323,7 @@ struct Builder {
     p.args.oks = oks;
     p.args.res_mask = n;
     p.args.twp_mask = (int64_t)code;
+    p.args.res_shift = k->two_step;
     p.args.xcd_remap = opt.xcd_remap;
     p.rader_n = n;
     p.label = label;
@@ -700,8 +701,22 @@ void axis_pass(Builder& b, int64_t n, int lmode, int smode, const Field* f, int 
 // ms, 1001^3 14.1 -> 11.2, 945^3 9.98 -> 8.85, 810^3 5.97 -> 5.59, 700^3
 // 3.80 -> 3.57; below it the rotation is the faster one: 675^3 3.06 against
 // 3.31 ms, 600^3 2.06 / 2.32, 1000 x 1000 x 300 2.82 / 3.05.  The rotation
-// stores rows a whole plane apart, the cycle one row length apart.
+// stores rows a whole plane apart, the cycle one row length apart.  Not where
+// two axes take Rader passes, whose permuted stores of misaligned rows do
+// better in the rotation (cycle / rotation): 769^3 7.29 / 6.18 ms, 1009^3
+// 19.3 / 17.8, 401 x 1009 x 1000 6.29 / 5.44, 769 x 1000 x 769 8.30 / 7.89;
+// with one it is the faster one still: 1009 x 1000 x 1000 13.0 / 13.7, 641 x
+// 1000 x 1024 8.14 / 8.72.
 constexpr int64_t kCycleBytes = int64_t(5) << 29;
+bool cycle_suits_other(const int64_t n[3], const Options& opt, int64_t split_max) {
+  int rader = 0;
+  for (int d = 0; d < 3; ++d) {
+    if (n[d] > split_max) return false;
+    rader += opt.rader && rader_length(n[d], opt.rader == 2);
+  }
+  return n[0] * n[1] * n[2] * 8 >= kCycleBytes && opt.pencil_order < 0 && rader < 2;
+}
+
 void pencil_cycled_other(Builder& b, const int64_t n[3]) {
   const int64_t A = n[0], B = n[1], C = n[2];
   const struct {
@@ -915,9 +930,8 @@ int build_passes(const int64_t n[3], int schedule, int layout, const Options& gi
              n[2] <= split_max) {
     pencil_swapped(b, n);
     assign_chain(passes, 0, need_ws);
-  } else if (resolved == DFT3D_SCHED_PENCIL && any_other && opt.pencil_order < 0 &&
-             total * 8 >= kCycleBytes && n[0] <= split_max && n[1] <= split_max &&
-             n[2] <= split_max) {
+  } else if (resolved == DFT3D_SCHED_PENCIL && any_other &&
+             cycle_suits_other(n, opt, split_max)) {
     pencil_cycled_other(b, n);
     assign_chain(passes, 0, need_ws);
   } else if (resolved == DFT3D_SCHED_PENCIL) {
@@ -1166,7 +1180,7 @@ void describe_list(std::ostringstream& os, const std::vector<Pass>& passes) {
     os << "],\"split\":[";
     if (p.k->two_step)  // two-step passes: the register DFTs the radices are grouped into
       os << p.k->two_step << ","
-         << (p.k->mixed ? p.args.res_mask : p.k->n) / p.k->two_step;
+         << (p.k->rader ? p.rader_n - 1 : p.k->mixed ? p.args.res_mask : p.k->n) / p.k->two_step;
     os << "]"
        << ",\"mfma_leaf\":" << p.k->mfma_leaf << ",\"threads\":" << p.k->threads
        << ",\"lds_bytes\":" << p.k->lds_bytes << ",\"pencils\":" << p.args.B

@@ -28,6 +28,7 @@ void register_kernels_bluestein_two_step_a(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_b(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_c(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_d(std::vector<KernelInfo>& v);
+void register_kernels_rader_two_step(std::vector<KernelInfo>& v);
 void register_kernels_two_step_power(std::vector<KernelInfo>& v);
 void register_kernels_two_step_a(std::vector<KernelInfo>& v);
 void register_kernels_two_step_b(std::vector<KernelInfo>& v);
@@ -61,6 +62,7 @@ const std::vector<KernelInfo>& kernel_registry() {
     register_kernels_bluestein_two_step_b(v);
     register_kernels_bluestein_two_step_c(v);
     register_kernels_bluestein_two_step_d(v);
+    register_kernels_rader_two_step(v);
     register_kernels_two_step_power(v);
     register_kernels_two_step_a(v);
     register_kernels_two_step_b(v);
@@ -270,7 +272,7 @@ const KernelInfo* find_rader_kernel(int64_t n, int tile) {
   const int variant = mixed_variant(code);
   const KernelInfo* best = nullptr;
   for (const KernelInfo& k : kernel_registry())
-    if (k.rader == variant && k.fixed_n == 0 && k.n >= n + 1 &&
+    if (k.rader == variant && !k.two_step && k.fixed_n == 0 && k.n >= n + 1 &&
         mixed_kernel_runs(variant, k.n, code)) {
       if (tile > 0 && k.tile == tile) return &k;
       if (!best || k.n < best->n) best = &k;

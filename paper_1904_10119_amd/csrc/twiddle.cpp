@@ -159,7 +159,7 @@ int64_t rader_generator(int64_t n) {
 
 int64_t rader_table_size(int64_t n) { return (n - 1) + (n - 1 + 1) / 2; }
 
-void make_rader_tables(int64_t n, float2* out) {
+void make_rader_tables(int64_t n, int a, float2* out) {
   const int64_t L = n - 1, g = rader_generator(n);
   std::vector<int64_t> pw(L);
   pw[0] = 1;
@@ -175,13 +175,16 @@ void make_rader_tables(int64_t n, float2* out) {
   for (int64_t k = 0; k < L; ++k) root_fp64(k, L, cr[k], ci[k]);  // w_L^k = cr - i ci
   for (int64_t k = 0; k < L; ++k) {
     double sr = 0.0, si = 0.0;
+    int64_t e = -k;  // m k mod L
     for (int64_t m = 0; m < L; ++m) {
-      const int64_t e = (m * k) % L;
+      e += k;
+      if (e >= L) e -= L;
       const double wr = cr[e], wi = -ci[e];
       sr += br[m] * wr - bi[m] * wi;
       si += br[m] * wi + bi[m] * wr;
     }
-    out[k] = make_float2((float)(sr / (double)L), (float)(si / (double)L));
+    const int64_t at = a ? k % a * (L / a) + k / a : k;
+    out[at] = make_float2((float)(sr / (double)L), (float)(si / (double)L));
   }
   int32_t* perm = reinterpret_cast<int32_t*>(out + L);
   for (int64_t j = 0; j < L; ++j) perm[j] = (int32_t)pw[j];
