@@ -101,6 +101,10 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 //  - 16, 32 and 64 along strided axes from 2^21 points up the pass kernel,
 //    whose 256, 128 or 64 pencils are long row segments (16 x 512 x 512 depth
 //    11.8 against 12.7, 32 x 256 x 512 10.9 against 13.0);
+//  - 16 and 32 from 2^25 points up the pass kernel in every order: the cycled
+//    pencil passes of such arrays read pencils a plane apart and write row
+//    segments of a tile's pencils (16 x 1024 x 2048 102 against 127, 32 x 1024
+//    x 1024 111 / 140; half the points 42 against 48 the other way round);
 //  - from 256 up, where tiles of 16 are at most 512 (two a CU), 8 pencils
 //    (16 x 256 x 256 8.3 / 7.2, 16 x 64 x 1024 12.2 / 9.1, 16 x 512 x 512 rows
 //    15.3 / 14.2; tiles of 4 gain no more, and at 1024 tiles 16 are faster:
@@ -111,6 +115,7 @@ const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, 
   if (n == 64 && points >= (int64_t(1) << 22)) tile = 32;
   if (n == 128 && points >= (int64_t(1) << 24)) return nullptr;
   if (n == 256 && points > (int64_t(1) << 25)) tile = 32;
+  if (n <= 32 && points >= (int64_t(1) << 25)) return nullptr;
   if (n <= 64 && lmode == MODE_COL && points >= (int64_t(1) << 21)) return nullptr;
   if (n >= 256 && pencils <= 16 * 512) tile = 8;
   for (const KernelInfo& k : kernel_registry())
