@@ -1,4 +1,4 @@
-// Lengths that are not powers of two: the DFT of length n as a circular
+// Lengths above 1024 that are not smooth: the DFT of length n as a circular
 // convolution of length m (a power of two, m >= 2n - 1) computed with two
 // power-of-two FFTs (Bluestein's chirp-z identity).  With the chirp
 // w[j] = exp(-pi i j^2 / n) and jk = (j^2 + k^2 - (k - j)^2) / 2,

@@ -1,4 +1,4 @@
-// Bluestein axes of length n <= 512 with a convolution length m = A B that
+// Bluestein axes of length n <= 1024 with a convolution length m = A B that
 // is not a power of two but the next of a ladder of products at least 2 n
 // (bluestein.h states the identity and the power-of-two form, which runs the
 // longer lengths): both FFTs of length m in two register steps, two
@@ -20,10 +20,16 @@
 // free index maps in the register DFTs, m = 512 = 16 x 32 and pointer steps
 // instead of products brought 99 to 85 us a pass.  Tiles of 16 pencils up to
 // m = 256 and of 8 above, where 16 leave two workgroups a CU (163^3 81 / 68
-// us, 211^3 217 / 160, 263^3 385 / 316; 83^3 19.8 / 20.1, 101^3 30.4 / 31.1).
+// us, 211^3 217 / 160, 263^3 385 / 316; 83^3 19.8 / 20.1, 101^3 30.4 / 31.1),
+// and of 4 above m = 1024, where the registers (118 to 150) leave three
+// wavefronts a SIMD and 4 pencils three workgroups a CU (8 / 4 pencils: 613 x
+// 613 x 64 514 / 404 us, 699 x 699 x 64 637 / 518, 557 x 557 x 64 333 / 338;
+// 6: 418 and 618; below m = 1024 8 pencils are 5 to 10 % ahead of 4).
 // Against the power-of-two form (MI355X, three passes): 61^3 24.5 -> 14.9 us,
 // 131^3 97.6 -> 48.7, 199^3 253 -> 131, 251^3 460 -> 254, 263^3 840 -> 316,
-// 379^3 2.07 -> 0.96 ms, 509^3 4.35 -> 2.46 ms.
+// 379^3 2.07 -> 0.96 ms, 509^3 4.35 -> 2.46 ms, 557 x 557 x 64 714 -> 338
+// us, 699 x 699 x 64 990 -> 518, 839 x 839 x 64 1324 -> 829, 1021 x 1021 x 64
+// 1785 -> 1196.
 //
 // PassArgs fields used: pencil fields and element strides as for every
 // pass, res_mask = n, res_shift = A.  Tables: tw[tm B + j] = w_m^{tm j};
@@ -207,14 +213,18 @@ KernelInfo kernel_info_bluestein_two_step(int smode) {
   return k;
 }
 
-// The convolution lengths A B: those products (A even, both at most 32)
-// whose operations a pencil no longer one undercuts.
+// The convolution lengths A B: up to 1024 those products (A even, both at
+// most 32) whose operations a pencil no longer one undercuts, above it eleven
+// whose factors the registers take (A up to 64, of which half is zero or not
+// wanted; B, whose DFT runs whole and twice, up to 32).
 constexpr int kBluesteinLadder[][2] = {
     {8, 8}, {6, 12}, {8, 10}, {8, 12}, {10, 10}, {12, 9}, {14, 8}, {12, 10}, {16,
     8}, {12, 12}, {16, 10}, {12, 14}, {16, 12}, {10, 20}, {12, 18}, {16, 14}, {12,
     20}, {16, 16}, {24, 12}, {16, 20}, {24, 14}, {24, 15}, {16, 24}, {20, 20}, {24,
     18}, {24, 20}, {16, 32}, {24, 24}, {24, 25}, {32, 20}, {24, 28}, {24, 30}, {24,
-    32}, {28, 28}, {28, 30}, {32, 28}, {32, 30}, {32, 32}};
+    32}, {28, 28}, {28, 30}, {32, 28}, {32, 30}, {32, 32}, {36,
+    30}, {48, 24}, {40, 30}, {40, 32}, {48, 28}, {48, 30}, {48, 32}, {56, 30}, {56,
+    32}, {60, 32}, {64, 32}};
 constexpr int kBluesteinLadderSize = sizeof(kBluesteinLadder) / sizeof(kBluesteinLadder[0]);
 
 // The kernels of ladder entries LO <= i < HI, for every order: lanes along
@@ -230,7 +240,7 @@ void add_bluestein_two_step(std::vector<KernelInfo>& v) {
     // shorter lengths take the entry before
     constexpr int NMIN =
         LO == 0 ? 1 : kBluesteinLadder[LO ? LO - 1 : 0][0] * kBluesteinLadder[LO ? LO - 1 : 0][1] / 2 + 1;
-    constexpr int T = A * B <= 256 ? 16 : 8;
+    constexpr int T = A * B <= 256 ? 16 : A * B <= 1024 ? 8 : 4;
     v.push_back(kernel_info_bluestein_two_step<A, B, NMIN, T, MODE_ROW>(MODE_COL));
     v.push_back(kernel_info_bluestein_two_step<A, B, NMIN, T, MODE_ROW>(MODE_ROW));
     v.push_back(kernel_info_bluestein_two_step<A, B, NMIN, T, MODE_COL>(MODE_COL));

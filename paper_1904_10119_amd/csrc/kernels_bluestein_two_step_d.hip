@@ -4,6 +4,6 @@
 
 namespace dft3d {
 void register_kernels_bluestein_two_step_d(std::vector<KernelInfo>& v) {
-  add_bluestein_two_step<32, kBluesteinLadderSize>(v);
+  add_bluestein_two_step<32, 38>(v);
 }
 }  // namespace dft3d

@@ -284,7 +284,7 @@ struct Builder {
   // pencils of fields f (bluestein.h documents the argument fields).
   void add_bluestein(int64_t n, const Field* f, int nf, int64_t ijs, int64_t oks,
                      const std::string& what, int lmode = MODE_ROW, int smode = MODE_COL) {
-    // two-step FFTs up to n = 512, power-of-two ones above
+    // two-step FFTs up to n = 1024, power-of-two ones above
     const KernelInfo* k = find_bluestein_two_step_kernel(n, lmode, smode);
     if (!k) k = find_bluestein_kernel((int)bluestein_length(n), opt.tile);
     const std::string label = what + " via " + std::to_string(k ? k->n : 0);

@@ -28,6 +28,7 @@ void register_kernels_bluestein_two_step_a(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_b(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_c(std::vector<KernelInfo>& v);
 void register_kernels_bluestein_two_step_d(std::vector<KernelInfo>& v);
+void register_kernels_bluestein_two_step_e(std::vector<KernelInfo>& v);
 void register_kernels_rader_two_step(std::vector<KernelInfo>& v);
 void register_kernels_two_step_power(std::vector<KernelInfo>& v);
 void register_kernels_two_step_a(std::vector<KernelInfo>& v);
@@ -62,6 +63,7 @@ const std::vector<KernelInfo>& kernel_registry() {
     register_kernels_bluestein_two_step_b(v);
     register_kernels_bluestein_two_step_c(v);
     register_kernels_bluestein_two_step_d(v);
+    register_kernels_bluestein_two_step_e(v);
     register_kernels_rader_two_step(v);
     register_kernels_two_step_power(v);
     register_kernels_two_step_a(v);

@@ -1,5 +1,5 @@
 """Bluestein axes with two-step FFTs of a convolution length m = A B (lengths
-up to 512): the chosen m and the steps' formulas on the CPU, GPU parity at
+up to 1024): the chosen m and the steps' formulas on the CPU, GPU parity at
 both ends of every m's range.
 
 Tolerance on the GPU: 2 log2(m) + 3 rounding levels for the axis (two FFTs
@@ -23,7 +23,7 @@ def axis_pass(n):
     return dft3d.describe((1, 1, n), "pencil", rader=0)["passes"][0]
 
 
-LENGTHS = [n for n in range(17, 513) if not smooth13(n)]
+LENGTHS = [n for n in range(17, 1024) if not smooth13(n)]
 
 
 def edge_lengths():
@@ -46,11 +46,12 @@ def test_convolution_lengths():
         assert 2 * n <= p["n"] <= max(64, 1 << int(np.ceil(np.log2(2 * n)))) and p["n"] >= last
         last = p["n"]
         assert p["threads"] >= p["tile"] * max(A, B) and p["lds_bytes"] <= 160 * 1024
-    assert axis_pass(514)["split"] == [] and axis_pass(514)["n"] == 2048
+    assert axis_pass(1031)["split"] == []
     assert dft3d.describe((1, 1, 251), "pencil", tile=4)["passes"][0]["bluestein"]
 
 
-@pytest.mark.parametrize("n", [17, 31, 37, 61, 101, 127, 131, 251, 263, 331, 509])
+@pytest.mark.parametrize("n", [17, 31, 37, 61, 101, 127, 131, 251, 263, 331, 509, 521, 557, 599, 613, 661, 701, 751, 821, 877,
+                               941, 1021])
 def test_steps_give_the_dft(n):
     """The three steps as the kernel documents them, in numpy."""
     A, B = axis_pass(n)["split"]
