@@ -119,18 +119,31 @@ int mixed_variant(uint64_t code);
 // kernel's radices (2, 3, 4, 5, 7, 8, 10, 11, 13, 16) whose product is at
 // most 2048 and that a compiled mixed-radix kernel runs at that length.
 bool radix_code_valid(uint64_t code);
-// The first step A of the split n = A B (A <= B <= 40, the most even one:
-// fewest registers) of a two-step pass (two_step_kernel.h); 0 for lengths
-// below 6 or above 1024, with a prime factor above 13, or without a split.
+// The first step A of the split n = A B (A <= B, the most even one: fewest
+// registers) of a two-step pass (two_step_kernel.h); 0 for lengths below 6 or
+// above 2000, with a prime factor above 13, or without a split of B <= 50 (B
+// <= 48 from 1700 up).  Measured, staged / two-step: 605 x 605 x 64 (B = 55) 292
+// / 327 us, 1750 x 1750 x 64 (35 x 50) 2057 / 2269, 1715 x 1715 x 64 (35 x 49)
+// 2024 / 2286; 1617 x 1617 x 64 (33 x 49) 2113 / 2019, 1029 x 1029 x 64 (21 x
+// 49) 840 / 713, 1920 x 1920 x 64 (40 x 48) 3628 / 2619.
 constexpr int two_step_split(int64_t n) {
-  if (n < 6 || n > 1024) return 0;
+  if (n < 6 || n > 2000) return 0;
   int64_t m = n;
   for (int f = 2; f <= 13; ++f)
     while (m % f == 0) m /= f;
   if (m != 1) return 0;
-  for (int a = 32; a >= 2; --a)
-    if (n % a == 0 && (int64_t)a * a <= n) return n / a <= 40 ? a : 0;
+  for (int a = 45; a >= 2; --a)
+    if (n % a == 0 && (int64_t)a * a <= n) return n / a <= (n < 1700 ? 50 : 48) ? a : 0;
   return 0;
+}
+// Pencils of a tile of the two-step pass of a length that splits: 16
+// (128-byte row segments) where they fit the LDS and B <= 40; 8 above, where
+// 16 would hold a wavefront to 128 registers and spill (343 x 343 x 64 176 us
+// in 16, 75 in 8; 1029 x 1029 x 64 1045 / 713).  Where both fit and B <= 40: 1152
+// x 1152 x 64 803 in 16, 932 in 8, 1080 x 100 x 100 104.5 / 101.4.
+constexpr int two_step_tile(int64_t n) {
+  const int64_t a = two_step_split(n), b = n / a;
+  return b <= 40 && 16 * ((a * (b | 1)) | 1) * 8 <= 160 * 1024 ? 16 : 8;
 }
 // The two-step kernel for length n and the load and store modes, or null.
 const KernelInfo* find_two_step_kernel(int64_t n, int lmode, int smode);

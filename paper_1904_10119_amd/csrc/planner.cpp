@@ -744,7 +744,9 @@ void pencil_cycled_other(Builder& b, const int64_t n[3]) {
 // half-written.  Measured, rotation / slab: 375 x 486 x 400 737 / 673 us,
 // 375^3 659 / 538, 455 x 325 x 195 339 / 270, 525^3 1878 / 1484, 105^3 22.5
 // / 20.9; longer misaligned passes 675^3 3.06 / 3.24 ms; aligned ones 324^3
-// 326 / 341 us, 600 x 600 x 18 64 / 72.  Below 2^20 points both are bound by
+// 326 / 341 us, 600 x 600 x 18 64 / 72; long axes in tiles of 8 pencils, whose
+// strided passes move 64-byte segments, 882 x 882 x 64 509 / 567, 1029 x 1029 x
+// 64 713 / 766 (686 x 686 x 64 329 / 279).  Below 2^20 points both are bound by
 // launches.
 bool slab_suits_other(const int64_t n[3], const Options& opt) {
   const int64_t total = n[0] * n[1] * n[2];
@@ -753,7 +755,7 @@ bool slab_suits_other(const int64_t n[3], const Options& opt) {
     return false;
   bool misaligned = false;
   for (int d = 0; d < 3; ++d) {
-    if (!two_step_split(n[d])) return false;
+    if (!two_step_split(n[d]) || (n[d] > 700 && two_step_tile(n[d]) < 16)) return false;
     misaligned = misaligned || (n[d] <= 640 && total / n[d] % 16 != 0);
   }
   return misaligned;

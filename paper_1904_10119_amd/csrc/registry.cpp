@@ -37,6 +37,10 @@ void register_kernels_two_step_c(std::vector<KernelInfo>& v);
 void register_kernels_two_step_d(std::vector<KernelInfo>& v);
 void register_kernels_two_step_e(std::vector<KernelInfo>& v);
 void register_kernels_two_step_f(std::vector<KernelInfo>& v);
+void register_kernels_two_step_g(std::vector<KernelInfo>& v);
+void register_kernels_two_step_h(std::vector<KernelInfo>& v);
+void register_kernels_two_step_i(std::vector<KernelInfo>& v);
+void register_kernels_two_step_j(std::vector<KernelInfo>& v);
 
 const std::vector<KernelInfo>& kernel_registry() {
   static const std::vector<KernelInfo> table = [] {
@@ -72,6 +76,10 @@ const std::vector<KernelInfo>& kernel_registry() {
     register_kernels_two_step_d(v);
     register_kernels_two_step_e(v);
     register_kernels_two_step_f(v);
+    register_kernels_two_step_g(v);
+    register_kernels_two_step_h(v);
+    register_kernels_two_step_i(v);
+    register_kernels_two_step_j(v);
     return v;
   }();
   return table;

@@ -22,11 +22,13 @@
 // point at n = 375, half of what the card issues at the copy rate), launch and
 // load latency below.  The tile is 16 pencils so that a COL row segment is
 // one 128-byte line: 400^3 takes 603 us so, 762 us in tiles of 8 pencils
-// (64-byte segments) and 629 us in tiles of 32 (fewer workgroups a CU).
+// (64-byte segments) and 629 us in tiles of 32 (fewer workgroups a CU);
+// two_step_tile says where 8 are taken.
 // Against the staged pass (same orders, MI355X): 96^3 25.0 -> 17.9 us, 90^3
 // 30.4 -> 18.7, 150^3 62.9 -> 32.6, 252^3 209 -> 141 (5.4 TB/s a pass),
 // 324^3 462 -> 326, 540^3 2370 -> 1481, 900^3 10.3 -> 8.6 ms, 640^3 2.95 ->
-// 2.75 ms; no faster at 1000^3 in the rotation's order (11.4 / 11.5 ms; 10.1
+// 2.75 ms, 1050 x 1050 x 64 847 -> 710 us, 1078 x 1078 x 64 1088 -> 777, 1536 x
+// 1536 x 64 2501 -> 1697; no faster at 1000^3 in the rotation's order (11.4 / 11.5 ms; 10.1
 // in the cycle, against 10.3).  A kernel for any length with a radix switch
 // took 177 us at 250^3 where the compiled lengths take 142: it holds the
 // registers of the largest radix (120 against 93).
@@ -204,8 +206,7 @@ void add_two_step_powers(std::vector<KernelInfo>& v) {
   add_two_step_power<N, T, MODE_COL, MODE_COL>(v);
 }
 
-// The kernels of the lengths LO <= n < HI that split, in tiles of 16 pencils
-// (128-byte row segments) for every order.
+// The kernels of the lengths LO <= n < HI that split, for every order.
 template <int LO, int HI>
 void add_two_step_kernels(std::vector<KernelInfo>& v) {
   if constexpr (HI - LO > 1) {
@@ -213,9 +214,10 @@ void add_two_step_kernels(std::vector<KernelInfo>& v) {
     add_two_step_kernels<(LO + HI) / 2, HI>(v);
   } else if constexpr (two_step_split(LO) > 0) {
     constexpr int A = two_step_split(LO), B = LO / A;
-    v.push_back(kernel_info_two_step<A, B, 16, MODE_ROW, MODE_COL>());
-    v.push_back(kernel_info_two_step<A, B, 16, MODE_ROW, MODE_ROW>());
-    v.push_back(kernel_info_two_step<A, B, 16, MODE_COL, MODE_COL>());
+    constexpr int T = two_step_tile(LO);
+    v.push_back(kernel_info_two_step<A, B, T, MODE_ROW, MODE_COL>());
+    v.push_back(kernel_info_two_step<A, B, T, MODE_ROW, MODE_ROW>());
+    v.push_back(kernel_info_two_step<A, B, T, MODE_COL, MODE_COL>());
   }
 }
 

@@ -11,7 +11,8 @@ import oracle
 from paper_1904_10119_amd import dft3d, inputs
 
 TWO_STEP = {6: [2, 3], 30: [5, 6], 96: [8, 12], 125: [5, 25], 143: [11, 13], 375: [15, 25],
-            486: [18, 27], 720: [24, 30], 1000: [25, 40], 1008: [28, 36], 1024: [32, 32]}
+            486: [18, 27], 720: [24, 30], 1000: [25, 40], 1008: [28, 36], 1024: [32, 32],
+            343: [7, 49], 1089: [33, 33], 1100: [25, 44], 1600: [40, 40], 1980: [44, 45]}
 
 
 def smooth13(n):
@@ -26,17 +27,22 @@ def first_pass(n, **kw):
 
 
 def test_which_lengths_split():
-    """Smooth lengths 6..1024 with a factor pair A <= B <= 40 take a two-step
-    pass with the most even pair; a tile option keeps the staged kernels."""
-    for n in range(2, 1101):
+    """Smooth lengths 6..2000 with a factor pair A <= B <= 50 (48 from 1700 up)
+    take a two-step pass with the most even pair, in tiles of 16 pencils where
+    B <= 40 and the LDS holds them, else 8; a tile option keeps the staged
+    kernels."""
+    for n in range(2, 2101):
         if n & (n - 1) == 0 or not smooth13(n):
             continue
         p = first_pass(n)
-        pairs = [a for a in range(2, 33) if n % a == 0 and a * a <= n and n // a <= 40]
-        assert p["split"] == ([max(pairs), n // max(pairs)] if pairs and 6 <= n <= 1024 else []), n
+        most = 50 if n < 1700 else 48
+        pairs = [a for a in range(2, 46) if n % a == 0 and a * a <= n and n // a <= most]
+        assert p["split"] == ([max(pairs), n // max(pairs)] if pairs and 6 <= n <= 2000 else []), n
         if p["split"]:
-            assert p["fixed_n"] == n and p["tile"] == 16
-            assert p["threads"] >= 16 * p["split"][1] and p["lds_bytes"] <= 160 * 1024
+            a, b = p["split"]
+            fits = b <= 40 and 16 * (a * (b | 1) | 1) * 8 <= 160 * 1024
+            assert p["fixed_n"] == n and p["tile"] == (16 if fits else 8)
+            assert p["threads"] >= p["tile"] * b and p["lds_bytes"] <= 160 * 1024
         assert first_pass(n, tile=16)["split"] == []
 
 
@@ -67,6 +73,7 @@ def test_auto_schedule_of_other_lengths():
         return dft3d.describe(shape, "auto", **kw)["schedule"]
     assert sched((375, 486, 400)) == "slab" and sched((105, 105, 105)) == "slab"
     assert sched((324, 324, 324)) == "pencil" and sched((400, 400, 400)) == "pencil"
+    assert sched((343, 343, 64)) == "slab" and sched((882, 882, 64)) == "pencil"
     assert sched((61, 75, 90)) == "pencil" and sched((101, 375, 375)) == "pencil"
     assert sched((675, 675, 675)) == "pencil" and sched((375, 375, 2048)) == "pencil"
     for kw in ({"tile": 16}, {"radices": [3, 5, 5, 5]}, {"pencil_order": 0}):
@@ -141,7 +148,9 @@ def bar(shape):
 @pytest.mark.parametrize("schedule", ["pencil", "slab"])
 @pytest.mark.parametrize("shape", [(6, 7, 30), (5, 17, 96), (125, 6, 16), (9, 143, 15),
                                    (3, 375, 33), (32, 486, 5), (720, 3, 7), (1, 1000, 17),
-                                   (1008, 5, 1), (1024, 3, 5), (3, 1024, 6), (105, 49, 27)])
+                                   (1008, 5, 1), (1024, 3, 5), (3, 1024, 6), (105, 49, 27),
+                                   (343, 3, 17), (5, 1089, 9), (1100, 3, 3), (3, 7, 1250),
+                                   (1600, 3, 3), (3, 1617, 3), (3, 3, 1980)])
 def test_two_step_passes_on_the_gpu(shape, schedule):
     """Smallest, largest and ragged cases of every order (rotating, rows,
     columns), whole and ragged tiles, forward and inverse."""
