@@ -588,14 +588,20 @@ __device__ __forceinline__ void mfma_finish(const float2* res, float2* dst, cons
 }
 
 // Waves per SIMD the one-tile form asks the compiler for: four (at most
-// 128 VGPRs) where two workgroups fit in a CU's LDS, else two.
+// 128 VGPRs) where two workgroups fit in a CU's LDS, else two; in tiles below
+// the default what the LDS holds, at most four.
 template <int N, int TE = mfma_tile_elems<N>()> constexpr int mfma_one_tile_waves() {
+  if (TE < mfma_tile_elems<N>()) {
+    const int fit = 160 * 1024 / ((mfma_buf_elems<N, TE>() + N) * 8) * mfma_threads<N, TE>() / 256;
+    return fit < 4 ? fit : 4;
+  }
   return (2 * (mfma_buf_elems<N, TE>() + N) * 8 <= 160 * 1024 || mfma_threads<N, TE>() >= 1024)
              ? 4 : 2;
 }
 
-// One tile per workgroup (TE tile elements: the default, or twice that in
-// the wide form, whose rotated store writes rows of twice the pencils).
+// One tile per workgroup (TE tile elements: the default, twice that in the
+// wide form, whose rotated store writes rows of twice the pencils, or less in
+// the narrow forms, which give small grids more workgroups).
 template <int N, int LM, int SM, int PREC, int L, int TE>
 __device__ __forceinline__ void fft_pass_mfma_run(
     const float2* src, float2* dst, const float2* __restrict__ tw,
@@ -730,6 +736,36 @@ KernelInfo kernel_info_mfma_wide() {
   k.mfma_leaf = L;
   k.mfma_wide = 1;
   return k;
+}
+
+// The narrow one-tile form (TE tile elements, less than the default):
+// find_mfma_kernel says where it is taken and what it measured.
+template <int N, int LM, int SM, int PREC, int L, int TE>
+KernelInfo kernel_info_mfma_narrow() {
+  static_assert(TE >= N && TE % 1024 == 0 && TE < mfma_tile_elems<N>(), "whole waves and pencils");
+  constexpr int LDS = (mfma_buf_elems<N, TE>() + N) * 8;
+  KernelInfo k{N, TE / N, LM, SM, 0, mfma_threads<N, TE>(), LDS,
+               &launch_mfma<N, LM, SM, PREC, L, TE>, 0, 0, PREC};
+  k.mfma_leaf = L;
+  k.mfma_wide = -1;
+  return k;
+}
+
+template <int N, int L, int PREC, int TE>
+void add_mfma_narrow_prec(std::vector<KernelInfo>& v) {
+  v.push_back(kernel_info_mfma_narrow<N, MODE_ROW, MODE_COL, PREC, L, TE>());
+  v.push_back(kernel_info_mfma_narrow<N, MODE_ROW, MODE_ROW, PREC, L, TE>());
+  v.push_back(kernel_info_mfma_narrow<N, MODE_COL, MODE_COL, PREC, L, TE>());
+}
+
+// The narrow form of every precision of one length and its default leaf.
+template <int N, int L, int TE>
+void add_mfma_narrow_kernels(std::vector<KernelInfo>& v) {
+  add_mfma_narrow_prec<N, L, DFT3D_PREC_BF16X1, TE>(v);
+  add_mfma_narrow_prec<N, L, DFT3D_PREC_FP16X1, TE>(v);
+  add_mfma_narrow_prec<N, L, DFT3D_PREC_BF16X6, TE>(v);
+  add_mfma_narrow_prec<N, L, DFT3D_PREC_BF16X9, TE>(v);
+  add_mfma_narrow_prec<N, L, DFT3D_PREC_FP16X3, TE>(v);
 }
 
 template <int N, int PREC, int L>

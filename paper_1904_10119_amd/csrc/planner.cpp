@@ -215,6 +215,8 @@ struct Builder {
       add_mixed(n, f, nf, ijs, oks, label + " radices", lmode, smode);
       return;
     }
+    int64_t pencils = 1;
+    for (int i = 0; i < nf; ++i) pencils *= f[i].count;
     const KernelInfo* k = nullptr;
     int leaf = 0;
     if (nt_side && opt.precision == DFT3D_PREC_FP32 && !tw)
@@ -231,14 +233,12 @@ struct Builder {
           opt.persistent &&
           (opt.nontemporal == 1 || (opt.nontemporal == 2 && total_points * 8 >= kStreamBytes &&
                                     default_mfma_persistent(n, opt.precision)));
-      k = find_mfma_kernel(n, lmode, smode, opt.precision, pers, opt.mfma_leaf, opt.tile);
+      k = find_mfma_kernel(n, pencils, lmode, smode, opt.precision, pers, opt.mfma_leaf, opt.tile);
       // a length without leaves of the asked length keeps its default leaves
       if (!k && opt.mfma_leaf)
-        k = find_mfma_kernel(n, lmode, smode, opt.precision, pers, 0, opt.tile);
+        k = find_mfma_kernel(n, pencils, lmode, smode, opt.precision, pers, 0, opt.tile);
       if (k) leaf = opt.precision;
     }
-    int64_t pencils = 1;
-    for (int i = 0; i < nf; ++i) pencils *= f[i].count;
     if (!k) k = pick_kernel(n, pencils, lmode, smode, tw, opt, total_points);
     if (!k) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;

@@ -16,6 +16,9 @@ void register_kernels_mfma_c(std::vector<KernelInfo>& v);
 void register_kernels_mfma_d(std::vector<KernelInfo>& v);
 void register_kernels_mfma_e(std::vector<KernelInfo>& v);
 void register_kernels_mfma_f(std::vector<KernelInfo>& v);
+void register_kernels_mfma_g(std::vector<KernelInfo>& v);
+void register_kernels_mfma_h(std::vector<KernelInfo>& v);
+void register_kernels_mfma_i(std::vector<KernelInfo>& v);
 void register_kernels_plane(std::vector<KernelInfo>& v);
 void register_kernels_fused(std::vector<KernelInfo>& v);
 void register_kernels_bluestein(std::vector<KernelInfo>& v);
@@ -55,6 +58,9 @@ const std::vector<KernelInfo>& kernel_registry() {
     register_kernels_mfma_d(v);
     register_kernels_mfma_e(v);
     register_kernels_mfma_f(v);
+    register_kernels_mfma_g(v);
+    register_kernels_mfma_h(v);
+    register_kernels_mfma_i(v);
     register_kernels_plane(v);
     register_kernels_fused(v);
     register_kernels_bluestein(v);
@@ -364,14 +370,40 @@ bool default_mfma_persistent(int n, int precision) {
   return false;
 }
 
-const KernelInfo* find_mfma_kernel(int n, int lmode, int smode, int precision,
+// Tile elements of the one-tile MFMA form: 8192 (4096 at length 4096) fill
+// the chip only from about 2^22 points on, two workgroups a CU.  Smaller grids
+// take less.  Measured on MI355X, bf16x6, us a pass at 2^17, 2^19, 2^20, 2^21 and
+// 2^22 points:
+//   length 64:   8192 5.9 6.9 9.3 10.1 14.4   1024 4.3 5.6 8.5 9.8 14.9   4096 4.7 5.9 8.4 9.5 14.2
+//   length 256:  8192 6.2 7.8 10.0 11.2 15.4  2048 4.4 6.5 9.6 11.3 15.0  4096 5.0 6.8 8.7 11.2 13.9
+//   length 512:  8192 8.4 9.0 10.8 15.7 19.1  2048 6.1 6.7 10.5 14.3 22.1  4096 6.2 6.7 8.2 14.0 19.3
+//   length 1024: 8192 8.9 9.4 10.2 13.1 20.6  2048 6.9 7.9 11.4 16.2 26.9  4096 6.9 7.5 9.4 14.0 21.4
+// and at 2^24 8192 is ahead at every length (256^3 55.2 against 59.3 in 4096).
+// Passes of lengths up to 128 that keep the layout stop at 2^20 (slab 256 x 128
+// x 64 34.2 in 8192, 35.3 in 4096).
+static int mfma_tile_points(int n, int64_t points, bool keeps) {
+  const int most = n == 1024 || (n <= 128 && keeps) ? 20 : n == 512 ? 21 : 22;
+  if (n > 1024 || points > (int64_t(1) << most)) return 0;
+  if (n > 256 || points > (int64_t(1) << 19)) return 4096;
+  return n == 256 ? 2048 : 1024;
+}
+
+const KernelInfo* find_mfma_kernel(int n, int64_t pencils, int lmode, int smode, int precision,
                                    int persistent, int leaf, int tile) {
+  // small grids: the narrow one-tile form of the default leaves, unless the
+  // persistent form, a tile or a leaf is asked for
+  if (tile <= 0 && !persistent && leaf == 0)
+    if (const int te = mfma_tile_points(n, pencils * n, lmode == smode))
+      for (const KernelInfo& k : kernel_registry())
+        if (k.mfma_wide < 0 && k.n == n && k.tile == te / n && k.lmode == lmode &&
+            k.smode == smode && k.precision == precision)
+          return &k;
   if (leaf == 0) leaf = default_mfma_leaf(n, precision);
   // the wide one-tile form where compiled (length 2048 rotated on write),
   // unless the persistent form or another tile is asked for
   if (tile > 0 || !persistent)
     for (const KernelInfo& k : kernel_registry())
-      if (k.mfma_wide && k.n == n && k.lmode == lmode && k.smode == smode &&
+      if (k.mfma_wide > 0 && k.n == n && k.lmode == lmode && k.smode == smode &&
           k.precision == precision && k.mfma_leaf == leaf && (tile <= 0 || k.tile == tile))
         return &k;
   const KernelInfo* other = nullptr;
