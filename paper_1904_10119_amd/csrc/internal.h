@@ -145,8 +145,15 @@ constexpr int two_step_tile(int64_t n) {
   const int64_t a = two_step_split(n), b = n / a;
   return b <= 40 && 16 * ((a * (b | 1)) | 1) * 8 <= 160 * 1024 ? 16 : 8;
 }
-// The two-step kernel for length n and the load and store modes, or null.
-const KernelInfo* find_two_step_kernel(int64_t n, int lmode, int smode);
+// Up to how many tiles of 16 pencils a two-step pass takes tiles of 8 instead:
+// where long pencils leave CUs idle.  Measured, 16 / 8 pencils, us a pass: 375
+// 36 tiles 5.9 / 5.2, 422 tiles 11.1 / 11.7; 585 36 tiles 7.6 / 6.2, 540 tiles
+// 26.5 / 21.8; 1000 36 tiles 9.7 / 7.9, 270 tiles 21.3 / 18.0; 150 and below
+// equal (4 pencils gain no more: 375 4.7, 585 25.4, 1000 18.1).
+constexpr int two_step_idle_tiles(int64_t n) { return n < 360 ? 0 : n < 512 ? 256 : 544; }
+// The two-step kernel for length n, a number of pencils and the load and
+// store modes, or null.
+const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, int smode);
 // Twiddles of a two-step pass: out[tm (n / a) + j] = w_n^{tm j}, from FP64.
 void make_two_step_twiddles(int64_t n, int a, float2* out);
 // The product of a radix code's stages.

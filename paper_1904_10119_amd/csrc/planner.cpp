@@ -341,7 +341,9 @@ struct Builder {
     // two register steps where the length splits into them, the staged
     // kernel for other lengths, an asked-for tile or radix sequence
     const KernelInfo* k = nullptr;
-    if (!asked && opt.tile <= 0) k = find_two_step_kernel(n, lmode, smode);
+    int64_t pencils = 1;
+    for (int i = 0; i < nf; ++i) pencils *= f[i].count;
+    if (!asked && opt.tile <= 0) k = find_two_step_kernel(n, pencils, lmode, smode);
     if (!k) k = find_mixed_kernel(n, code, opt.tile, lmode, smode);
     if (!k || !code) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;

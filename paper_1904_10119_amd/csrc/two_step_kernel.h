@@ -206,18 +206,24 @@ void add_two_step_powers(std::vector<KernelInfo>& v) {
   add_two_step_power<N, T, MODE_COL, MODE_COL>(v);
 }
 
-// The kernels of the lengths LO <= n < HI that split, for every order.
+template <int A, int B, int T>
+void add_two_step_modes(std::vector<KernelInfo>& v) {
+  v.push_back(kernel_info_two_step<A, B, T, MODE_ROW, MODE_COL>());
+  v.push_back(kernel_info_two_step<A, B, T, MODE_ROW, MODE_ROW>());
+  v.push_back(kernel_info_two_step<A, B, T, MODE_COL, MODE_COL>());
+}
+
+// The kernels of the lengths LO <= n < HI that split, for every order, in the
+// tiles find_two_step_kernel picks from.
 template <int LO, int HI>
 void add_two_step_kernels(std::vector<KernelInfo>& v) {
   if constexpr (HI - LO > 1) {
     add_two_step_kernels<LO, (LO + HI) / 2>(v);
     add_two_step_kernels<(LO + HI) / 2, HI>(v);
   } else if constexpr (two_step_split(LO) > 0) {
-    constexpr int A = two_step_split(LO), B = LO / A;
-    constexpr int T = two_step_tile(LO);
-    v.push_back(kernel_info_two_step<A, B, T, MODE_ROW, MODE_COL>());
-    v.push_back(kernel_info_two_step<A, B, T, MODE_ROW, MODE_ROW>());
-    v.push_back(kernel_info_two_step<A, B, T, MODE_COL, MODE_COL>());
+    constexpr int A = two_step_split(LO), B = LO / A, T = two_step_tile(LO);
+    add_two_step_modes<A, B, T>(v);
+    if constexpr (T == 16 && two_step_idle_tiles(LO) > 0) add_two_step_modes<A, B, 8>(v);
   }
 }
 

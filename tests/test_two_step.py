@@ -41,9 +41,13 @@ def test_which_lengths_split():
         if p["split"]:
             a, b = p["split"]
             fits = b <= 40 and 16 * (a * (b | 1) | 1) * 8 <= 160 * 1024
-            assert p["fixed_n"] == n and p["tile"] == (16 if fits else 8)
+            assert p["fixed_n"] == n and p["tile"] == (16 if fits and n < 360 else 8)
             assert p["threads"] >= p["tile"] * b and p["lds_bytes"] <= 160 * 1024
         assert first_pass(n, tile=16)["split"] == []
+    # tiles of 8 where 16 leave CUs idle: up to 256 tiles, from 512 up to 544
+    for n, m in ((375, 64), (500, 64), (585, 136), (1000, 136), (1100, 136)):
+        tiles = [dft3d.describe((k, 64, n), "pencil")["passes"][0]["tile"] for k in (m, m + 1)]
+        assert tiles == ([8, 16] if n != 1100 else [8, 8]), n
 
 
 @pytest.mark.parametrize("n", sorted(TWO_STEP))
