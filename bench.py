@@ -262,7 +262,9 @@ def traffic_from_profile(path):
                   if l.startswith(("traffic_bytes_per_launch: ",
                                    "kernel_source_sha256_16: ")))
     src = b"".join(open(os.path.join(ROOT, "paper_1904_10119_amd", "csrc", f),
-                        "rb").read() for f in ("pass_kernel.h", "fft_device.h"))
+                        "rb").read()
+                   for f in ("pass_kernel.h", "fft_device.h", "mixed_kernel.h",
+                             "two_step_kernel.h"))
     if hashlib.sha256(src).hexdigest()[:16] != fields.get("kernel_source_sha256_16"):
         return None
     return float(fields["traffic_bytes_per_launch"])

@@ -98,7 +98,10 @@ enum dft3d_status {
  * an option rebuilds the pass list (host work plus a table upload). */
 enum dft3d_option {
   DFT3D_OPT_PRECISION = 1,   /* enum dft3d_precision; default FP32 */
-  DFT3D_OPT_TILE = 2,        /* pencils per workgroup, power of two; 0 = default */
+  DFT3D_OPT_TILE = 2,        /* pencils per workgroup, power of two; 0 = default
+                                (Bluestein passes up to 1024 points and
+                                split-precision passes have one tile per
+                                length, or size of grid, and ignore it) */
   DFT3D_OPT_XCD_REMAP = 3,   /* 1 = map consecutive tiles to one XCD; default 1 */
   DFT3D_OPT_SPLIT_MAX = 4,   /* longest axis done in one pass; longer axes
                                 are split four-step; 0 = default */
@@ -175,8 +178,8 @@ enum dft3d_option {
                                 passes of length n without a four-step
                                 twiddle then run the mixed-radix kernel
                                 with these stages (powers of two too); other
-                                lengths keep their default.  0 = default
-                                (the compiled sequence of each length).
+                                lengths keep their default.  0, or the
+                                sequence the length has anyway, = default.
                                 Workgroup size is set by DFT3D_OPT_TILE:
                                 pencils per workgroup times the kernel's
                                 threads per pencil.  Other values:
@@ -186,7 +189,7 @@ enum dft3d_option {
                                 as a cyclic convolution of length n - 1
                                 done with two mixed-radix FFTs of that
                                 length, instead of Bluestein (two FFTs of
-                                the power of two >= 2n - 1).  1 (default) =
+                                a length of at least 2n - 1).  1 (default) =
                                 Rader for the primes a kernel is compiled
                                 for, 2 = for every such prime (a generic
                                 kernel for the others, measured slower than
@@ -204,7 +207,10 @@ enum dft3d_option {
                                 bytes) and 2048 (16).  1 (default) = on,
                                 0 = the whole-length kernels.  Taken when
                                 DFT3D_OPT_TILE is 0 or the halves kernel's
-                                tile.  Other values: INVALID_ARG */
+                                tile, and not where fewer than 256 such
+                                tiles would leave compute units idle (above
+                                2^16 points, tile 0).  Other values:
+                                INVALID_ARG */
   DFT3D_OPT_PENCIL_ORDER = 17, /* pencil schedule, every axis a power of two
                                 and unsplit: the intermediate orders, all
                                 ending in the natural order.  0 = each pass
@@ -219,7 +225,8 @@ enum dft3d_option {
                                 arrays with an axis of 2048, else 0 (the
                                 faster order measured for each).  Arrays
                                 with other lengths keep the rotation, and
-                                with -1 run the cycle from 2.5 GiB up.
+                                with -1 run the cycle from 2.5 GiB up
+                                (fewer than two axes on Rader passes).
                                 Other values: INVALID_ARG */
   DFT3D_OPT_NUM_PASSES = 100 /* read-only: number of kernel launches */
 };
@@ -239,18 +246,18 @@ const char* dft3d_status_string(int status);
  * the natural layout on every schedule, one pass per
  * such axis (rotate-on-write in the pencil schedule, in layout in the slab
  * and volumetric schedules): a mixed-radix pass when every prime factor of
- * n_d is at most 13 (in two register steps where n_d <= 1024 splits into two
- * factors of at most 40, else in stages of radix 2, 3, 4, 5, 7, 8, 10, 11,
+ * n_d is at most 13 (in two register steps where n_d <= 2000 splits into two
+ * factors of at most 50, 48 from 1700 up, else in stages of radix 2, 3, 4, 5, 7, 8, 10, 11,
  * 13, 16), else for
  * the primes n_d whose n_d - 1 has that property and that a Rader kernel is
  * compiled for a Rader pass (a circular convolution of length n_d - 1 done
- * with two mixed-radix FFTs, see DFT3D_OPT_RADER), else a Bluestein pass (the DFT of length n as a circular
- * convolution of length m, the power of two >= 2n - 1, up to 8192, done
- * with two power-of-two FFTs in the same workgroup).  Split precisions, the shuffled layout and
- * move-only plans with such lengths return UNSUPPORTED_SCHEDULE.  The
- * workspace is N * 8 bytes as for powers of two.  Validates the arguments
- * first
- * (INVALID_ARG / UNSUPPORTED_SIZE / UNSUPPORTED_SCHEDULE), then needs a HIP
+ * with two mixed-radix FFTs, see DFT3D_OPT_RADER), else a Bluestein pass (the
+ * DFT of length n as a circular convolution of length m done with two FFTs in
+ * the same workgroup: up to n = 1024 m is the next of a ladder of products
+ * m >= 2n, above it the power of two >= 2n - 1, up to 8192).  Split
+ * precisions, the shuffled layout and move-only plans with such lengths
+ * return UNSUPPORTED_SCHEDULE.  The workspace is N * 8 bytes as for powers of
+ * two.  Validates the arguments first (INVALID_ARG / UNSUPPORTED_SIZE / UNSUPPORTED_SCHEDULE), then needs a HIP
  * device (NO_DEVICE), then allocates and uploads the twiddle tables on the
  * current device (OUT_OF_MEMORY / HIP_ERROR).  *out receives the handle, or
  * NULL on error.  The workspace is not allocated here. */
