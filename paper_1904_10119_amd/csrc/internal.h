@@ -180,7 +180,7 @@ void make_rader_tables(int64_t n, int a, float2* out);
 const KernelInfo* find_bluestein_kernel(int m, int tile);
 // The Bluestein kernel with two-step FFTs for length n and the load and
 // store modes: the shortest convolution length >= 2 n compiled; null if
-// none (n > 512).
+// none (n > 1024).
 const KernelInfo* find_bluestein_two_step_kernel(int64_t n, int lmode, int smode);
 // The fused volumetric two-axis kernel for split factor a, if compiled
 // (contig: V2 runs contiguous in memory; the persistent form if asked for;

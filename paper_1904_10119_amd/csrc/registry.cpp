@@ -110,7 +110,8 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 // 251 / 246 and 1024^3 10.49 / 10.26 ms (whole transform).
 // Tiles of 16 pencils, with these exceptions:
 //  - 64 from 2^22 points up 32 pencils (64 x 512 x 512 43.0 / 41.9);
-//  - 128 from 2^24 points up the 32-pencil pass kernel (512 x 512 x 128 rows
+//  - 128 from 2^23 points up the 32-pencil pass kernel (64 x 1024 x 128 rows
+//    29.3 against 33.0, 256 x 256 x 128 30.0 / 32.9; 512 x 512 x 128 rows
 //    95.8 against 101 us with two steps in 32 pencils, 104 in 16);
 //  - 256 above 2^25 points 32 pencils (1024 x 512 x 256 437 / 412; below, 16
 //    are faster: 128 x 1024 x 256 rows 97.6 against 103.7);
@@ -129,7 +130,7 @@ const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, 
   const int64_t points = pencils * n;
   int tile = 16;
   if (n == 64 && points >= (int64_t(1) << 22)) tile = 32;
-  if (n == 128 && points >= (int64_t(1) << 24)) return nullptr;
+  if (n == 128 && points >= (int64_t(1) << 23)) return nullptr;
   if (n == 256 && points > (int64_t(1) << 25)) tile = 32;
   if (n <= 32 && points >= (int64_t(1) << 25)) return nullptr;
   if (n <= 64 && lmode == MODE_COL && points >= (int64_t(1) << 21)) return nullptr;
