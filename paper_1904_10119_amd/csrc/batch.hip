@@ -33,23 +33,24 @@ int device_cu_count();
 
 namespace {
 
-template <int LM>
+template <int LM, int ONE>
 int batch_tile_of(int n) {
   switch (n) {
-    case 1: return batch_tile<1, LM>();
-    case 2: return batch_tile<2, LM>();
-    case 4: return batch_tile<4, LM>();
-    case 8: return batch_tile<8, LM>();
-    case 16: return batch_tile<16, LM>();
-    case 32: return batch_tile<32, LM>();
-    case 64: return batch_tile<64, LM>();
-    case 128: return batch_tile<128, LM>();
-    case 256: return batch_tile<256, LM>();
+    case 1: return batch_tile<1, LM, ONE>();
+    case 2: return batch_tile<2, LM, ONE>();
+    case 4: return batch_tile<4, LM, ONE>();
+    case 8: return batch_tile<8, LM, ONE>();
+    case 16: return batch_tile<16, LM, ONE>();
+    case 32: return batch_tile<32, LM, ONE>();
+    case 64: return batch_tile<64, LM, ONE>();
+    case 128: return batch_tile<128, LM, ONE>();
+    case 256: return batch_tile<256, LM, ONE>();
     default: return 0;
   }
 }
-int batch_tile_for(int n, int lmode) {
-  return lmode == MODE_ROW ? batch_tile_of<MODE_ROW>(n) : batch_tile_of<MODE_COL>(n);
+int batch_tile_for(int n, int lmode, bool persistent) {
+  if (persistent) return batch_tile_of<MODE_COL, 1>(n);  // one tile for every order
+  return lmode == MODE_ROW ? batch_tile_of<MODE_ROW, 0>(n) : batch_tile_of<MODE_COL, 0>(n);
 }
 
 // One launch of the level form: the 1D items or one class of plane items of
@@ -71,7 +72,7 @@ bool batchable(const std::vector<Pass>& passes, bool persistent) {
       continue;
     }
     if (ps.k->n > kBatchMaxN || ps.k->post_twiddle) return false;
-    if (batch_tile_for(ps.k->n, ps.k->lmode) == 0) return false;
+    if (batch_tile_for(ps.k->n, ps.k->lmode, persistent) == 0) return false;
   }
   return true;
 }
@@ -81,9 +82,9 @@ bool batchable(const std::vector<Pass>& passes, bool persistent) {
 // first / ntiles / dep / n / n1 / modes / args are filled, buffer and table
 // pointers are left null.  Item k belongs to problem item_plan[k], pass
 // item_pass[k]; its dep is the item of the same problem one level earlier.
-int batch_layout(const std::vector<const std::vector<Pass>*>& lists, std::vector<BatchItem>& items,
-                 std::vector<int>& item_plan, std::vector<int>& item_pass,
-                 std::vector<Level>& levels) {
+int batch_layout(const std::vector<const std::vector<Pass>*>& lists, bool persistent,
+                 std::vector<BatchItem>& items, std::vector<int>& item_plan,
+                 std::vector<int>& item_pass, std::vector<Level>& levels) {
   const int count = (int)lists.size();
   size_t nlev = 0;
   for (const auto* l : lists) nlev = std::max(nlev, l->size());
@@ -111,7 +112,7 @@ int batch_layout(const std::vector<const std::vector<Pass>*>& lists, std::vector
         if (planes) {
           it.ntiles = ps.args.B;
         } else {
-          const int T = batch_tile_for(it.n, it.lmode);
+          const int T = batch_tile_for(it.n, it.lmode, persistent);
           it.ntiles = (ps.args.B + T - 1) / T;
         }
         it.first = first;
@@ -300,7 +301,7 @@ int build_batch(BatchGraph* g, dft3d_plan_s* const* plans, int count, bool persi
   g->persistent = persistent;
   std::vector<const std::vector<Pass>*> lists;
   for (int i = 0; i < count; ++i) lists.push_back(&plans[i]->passes);
-  int st = batch_layout(lists, g->items, g->item_plan, g->item_pass, g->levels);
+  int st = batch_layout(lists, persistent, g->items, g->item_plan, g->item_pass, g->levels);
   if (st != DFT3D_OK) return st;
   for (size_t k = 0; k < g->items.size(); ++k) {
     const dft3d_plan_s* p = plans[g->item_plan[k]];
@@ -589,7 +590,8 @@ std::string batch_describe(const std::vector<const std::vector<Pass>*>& lists,
   std::vector<int> item_plan, item_pass;
   std::vector<Level> levels;
   int64_t total = 0;
-  if (all && batch_layout(lists, items, item_plan, item_pass, levels) != DFT3D_OK) all = false;
+  if (all && batch_layout(lists, persistent, items, item_plan, item_pass, levels) != DFT3D_OK)
+    all = false;
   for (const BatchItem& it : items) total += it.ntiles;
   os << ",\"total\":" << total << ",\"items\":[";
   for (size_t k = 0; k < items.size(); ++k) {
@@ -597,7 +599,7 @@ std::string batch_describe(const std::vector<const std::vector<Pass>*>& lists,
     os << (k ? "," : "") << "{\"problem\":" << item_plan[k] << ",\"pass\":" << item_pass[k]
        << ",\"first\":" << it.first << ",\"ntiles\":" << it.ntiles << ",\"dep\":" << it.dep
        << ",\"n\":" << it.n << ",\"n1\":" << it.n1 << ",\"pencils\":" << it.a.B
-       << ",\"tile\":" << (it.n1 ? 1 : batch_tile_for(it.n, it.lmode)) << "}";
+       << ",\"tile\":" << (it.n1 ? 1 : batch_tile_for(it.n, it.lmode, persistent)) << "}";
   }
   os << "],\"levels\":[";
   for (size_t k = 0; k < levels.size(); ++k) {

@@ -33,14 +33,21 @@ constexpr int kBatchThreads = 256;
 // Longest transform length a batched item may have.
 constexpr int kBatchMaxN = 256;
 
-// Contiguous axes from length 16 up run in the two register steps a plan's
-// own passes take (a butterfly of step 1 a thread); strided axes, whose row
-// segments are the tile, and shorter lengths run the pass kernel's stages in
-// its larger tiles (96 problems of {32, 64, 128}^3, two steps everywhere: 286
-// against 280 us).
-template <int N, int LM> constexpr bool batch_two_step() { return N >= 16 && LM == MODE_ROW; }
-template <int N, int LM> constexpr int batch_tile() {
-  if constexpr (batch_two_step<N, LM>())
+// In the level form (ONE = 0) contiguous axes from length 16 up run in the two
+// register steps of a plan's own passes (a butterfly of step 1 a thread), so
+// that a problem of a batch keeps the bits of its own plan; strided axes,
+// whose row segments are the tile, and shorter lengths run the pass kernel's
+// stages in its larger tiles (96 problems of {32, 64, 128}^3, two steps
+// everywhere: 286 against 280 us).  The one-launch form (ONE = 1) runs the
+// pass kernel's stages throughout: each tile costs it a device-scope release
+// and acquire, so the larger tile wins (two steps / stages, the same 96
+// problems 4.98 / 4.48 ms, as pencil plans 8.44 / 5.67; 64 pencil problems of
+// {16, 32}^3 374 / 164 us).
+template <int N, int LM, int ONE> constexpr bool batch_two_step() {
+  return !ONE && N >= 16 && LM == MODE_ROW;
+}
+template <int N, int LM, int ONE> constexpr int batch_tile() {
+  if constexpr (batch_two_step<N, LM, ONE>())
     return kBatchThreads / (N / two_step_split(N));
   else
     return kBatchThreads / (N / Blocking<N>::E);
@@ -77,23 +84,29 @@ struct BatchState {
   unsigned int error;       // set when a bounded wait runs out
 };
 
-// LDS bytes of the largest tile the batched kernel runs.
+// LDS elements of the largest 1D tile of either form.
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
-template <int N> constexpr int batch_lds_elems() {
-  constexpr int T = batch_tile<N, MODE_COL>();
-  return cmax(batch_tile<N, MODE_ROW>() *
-                  two_step_stride(two_step_split(N), N / two_step_split(N)),
-              num_stages<Blocking<N>>() > 1 ? T * lds_pencil_stride<N, T>() : 1);
+template <int N, int ONE> constexpr int batch_lds_elems() {
+  constexpr int T = batch_tile<N, MODE_COL, ONE>();
+  constexpr int pass = num_stages<Blocking<N>>() > 1 ? T * lds_pencil_stride<N, T>() : 1;
+  if constexpr (batch_two_step<N, MODE_ROW, ONE>())
+    return cmax(batch_tile<N, MODE_ROW, ONE>() *
+                    two_step_stride(two_step_split(N), N / two_step_split(N)),
+                pass);
+  else
+    return pass;
 }
-constexpr int kBatchLdsElems =
-    cmax(cmax(cmax(batch_lds_elems<256>(), batch_lds_elems<128>()), batch_lds_elems<64>()),
-         cmax(batch_lds_elems<32>(), batch_lds_elems<16>()));
+template <int ONE> constexpr int batch_lds() {
+  return cmax(cmax(cmax(batch_lds_elems<256, ONE>(), batch_lds_elems<128, ONE>()),
+                   batch_lds_elems<64, ONE>()),
+              cmax(batch_lds_elems<32, ONE>(), batch_lds_elems<16, ONE>()));
+}
 
-template <int N, int LM, int SM>
+template <int N, int LM, int SM, int ONE>
 __device__ __forceinline__ void batch_tile_run(const BatchItem& it, int64_t tile, float2* lds) {
-  constexpr int T = batch_tile<N, LM>();
+  constexpr int T = batch_tile<N, LM, ONE>();
   const int tid = threadIdx.x;
-  if constexpr (batch_two_step<N, LM>()) {
+  if constexpr (batch_two_step<N, LM, ONE>()) {
     constexpr int A = two_step_split(N), B = N / A;
     static_assert(T * B == kBatchThreads && A <= B, "a butterfly of step 1 a thread");
     two_step_first<A, B, T, LM, kRoots>(it.src, it.a, tile, lds, tid);
@@ -113,15 +126,15 @@ __device__ __forceinline__ void batch_tile_run(const BatchItem& it, int64_t tile
   }
 }
 
-template <int N>
+template <int N, int ONE>
 __device__ __forceinline__ void batch_tile_modes(const BatchItem& it, int64_t tile,
                                                  float2* lds) {
   if (it.lmode == MODE_ROW && it.smode == MODE_COL)
-    batch_tile_run<N, MODE_ROW, MODE_COL>(it, tile, lds);
+    batch_tile_run<N, MODE_ROW, MODE_COL, ONE>(it, tile, lds);
   else if (it.lmode == MODE_ROW)
-    batch_tile_run<N, MODE_ROW, MODE_ROW>(it, tile, lds);
+    batch_tile_run<N, MODE_ROW, MODE_ROW, ONE>(it, tile, lds);
   else
-    batch_tile_run<N, MODE_COL, MODE_COL>(it, tile, lds);
+    batch_tile_run<N, MODE_COL, MODE_COL, ONE>(it, tile, lds);
 }
 
 // Relaxed device-scope load: reads the coherent value without the L2
@@ -145,7 +158,7 @@ batch_upload_kernel(const unsigned long long* host, unsigned long long* dev, int
 __global__ void __launch_bounds__(kBatchThreads)
 batch_level_kernel(const BatchItem* __restrict__ items, int item_lo, int item_hi,
                    int64_t base) {
-  __shared__ float2 lds[kBatchLdsElems];
+  __shared__ float2 lds[batch_lds<0>()];
   const int64_t ticket = base + blockIdx.x;
   int lo = item_lo, hi = item_hi - 1;
   while (lo < hi) {
@@ -155,15 +168,15 @@ batch_level_kernel(const BatchItem* __restrict__ items, int item_lo, int item_hi
   const BatchItem& it = items[lo];
   const int64_t tile = ticket - it.first;
   switch (it.n) {
-    case 1: batch_tile_modes<1>(it, tile, lds); break;
-    case 2: batch_tile_modes<2>(it, tile, lds); break;
-    case 4: batch_tile_modes<4>(it, tile, lds); break;
-    case 8: batch_tile_modes<8>(it, tile, lds); break;
-    case 16: batch_tile_modes<16>(it, tile, lds); break;
-    case 32: batch_tile_modes<32>(it, tile, lds); break;
-    case 64: batch_tile_modes<64>(it, tile, lds); break;
-    case 128: batch_tile_modes<128>(it, tile, lds); break;
-    default: batch_tile_modes<256>(it, tile, lds); break;
+    case 1: batch_tile_modes<1, 0>(it, tile, lds); break;
+    case 2: batch_tile_modes<2, 0>(it, tile, lds); break;
+    case 4: batch_tile_modes<4, 0>(it, tile, lds); break;
+    case 8: batch_tile_modes<8, 0>(it, tile, lds); break;
+    case 16: batch_tile_modes<16, 0>(it, tile, lds); break;
+    case 32: batch_tile_modes<32, 0>(it, tile, lds); break;
+    case 64: batch_tile_modes<64, 0>(it, tile, lds); break;
+    case 128: batch_tile_modes<128, 0>(it, tile, lds); break;
+    default: batch_tile_modes<256, 0>(it, tile, lds); break;
   }
 }
 
@@ -217,7 +230,7 @@ batch_plane_level_kernel(const BatchItem* __restrict__ items, int item_lo, int i
 }
 
 // LDS of the persistent kernel: the largest 1D tile or small plane.
-constexpr int kBatchPersistentLds = cmax(kBatchLdsElems, plane_lds_elems<128, 32>());
+constexpr int kBatchPersistentLds = cmax(batch_lds<1>(), plane_lds_elems<128, 32>());
 
 // Plane shapes the persistent kernel runs (small planes, 256 threads).
 __host__ __device__ constexpr bool batch_persistent_plane_shape(int n1, int n2) {
@@ -259,7 +272,7 @@ __device__ __noinline__ void batch_small_plane(const BatchItem& it, int64_t plan
 // at once.
 template <int N>
 __device__ __noinline__ void batch_tile_call(const BatchItem& it, int64_t tile, float2* lds) {
-  batch_tile_modes<N>(it, tile, lds);
+  batch_tile_modes<N, 1>(it, tile, lds);
 }
 
 // Wave-uniform copies (lane 0's value) of values every lane holds alike.
