@@ -226,7 +226,8 @@ enum dft3d_option {
                                 faster order measured for each).  Arrays
                                 with other lengths keep the rotation, and
                                 with -1 run the cycle from 2.5 GiB up
-                                (fewer than two axes on Rader passes).
+                                (fewer than two axes on Rader passes, none
+                                of 2048).
                                 Other values: INVALID_ARG */
   DFT3D_OPT_NUM_PASSES = 100 /* read-only: number of kernel launches */
 };

@@ -708,12 +708,17 @@ void axis_pass(Builder& b, int64_t n, int lmode, int smode, const Field* f, int 
 // better in the rotation (cycle / rotation): 769^3 7.29 / 6.18 ms, 1009^3
 // 19.3 / 17.8, 401 x 1009 x 1000 6.29 / 5.44, 769 x 1000 x 769 8.30 / 7.89;
 // with one it is the faster one still: 1009 x 1000 x 1000 13.0 / 13.7, 641 x
-// 1000 x 1024 8.14 / 8.72.
+// 1000 x 1024 8.14 / 8.72.  Not with an axis of 2048 either, whose pass is the
+// two-halves kernel in the rotation but a staged mixed-radix one under the
+// general pencil index of the cycle (cycle / rotation): 2048 x 1000 x 300 7.45
+// / 6.37 ms, 1000 x 2048 x 200 5.02 / 3.93, 2048 x 500 x 500 6.52 / 5.13, 2048 x
+// 2048 x 375 19.3 / 16.7 (only 2048 x 1031 x 1031, with two long Bluestein axes,
+// does better in the cycle, 105 / 114).
 constexpr int64_t kCycleBytes = int64_t(5) << 29;
 bool cycle_suits_other(const int64_t n[3], const Options& opt, int64_t split_max) {
   int rader = 0;
   for (int d = 0; d < 3; ++d) {
-    if (n[d] > split_max) return false;
+    if (n[d] > split_max || (is_pow2(n[d]) && n[d] >= 2048)) return false;
     rader += opt.rader && rader_length(n[d], opt.rader == 2);
   }
   return n[0] * n[1] * n[2] * 8 >= kCycleBytes && opt.pencil_order < 0 && rader < 2;
