@@ -151,6 +151,23 @@ constexpr int two_step_tile(int64_t n) {
 // 26.5 / 21.8; 1000 36 tiles 9.7 / 7.9, 270 tiles 21.3 / 18.0; 150 and below
 // equal (4 pencils gain no more: 375 4.7, 585 25.4, 1000 18.1).
 constexpr int two_step_idle_tiles(int64_t n) { return n < 360 ? 0 : n < 512 ? 256 : 544; }
+// Tiles of 64 or 32 pencils of the lengths 48..127 on large grids, where tiles
+// of 16 write and read row segments of only one line: from 2^17 pencils up 64
+// pencils where the second factor is at most 12 (a workgroup of at most 768
+// threads), else 32, and from 2^19 pencils 64 up to a factor of 16 too.
+// Measured, 16 / 32 / 64 pencils, us a pass: 72 of 72 x 512 x 512 70.4 / 60.5 /
+// 52.6, 60 of 1024 x 1024 x 60 206 / 194 / 185, 96 of 701 x 703 x 96 (rows off the
+// lines) 172 / 147 / 135, 112 of 512 x 112 x 512 92.9 / 86.7 / 89.6 and of 1001 x
+// 999 x 112 444 / 369 / 348, 125 of 125 x 512 x 512 119.9 / 101.7; in layout 700 x
+// 96 x 700 155 / 133 / 128.  The staged pass in 64 pencils: 55.8, 196, 132, 85.8,
+// 348, 110.5, 150.  At 2^16 pencils 16 are level or ahead (256 x 256 x 100 22.6 /
+// 21.8 / 24.1, 300 x 96 x 360 29.8 / 30.7 / 31.0).
+constexpr int64_t kTwoStepWidePencils = int64_t(1) << 17;
+constexpr int two_step_wide_tile(int64_t n, int64_t pencils) {
+  if (n < 48 || n >= 128 || pencils < kTwoStepWidePencils) return 0;
+  const int64_t b = n / two_step_split(n);
+  return b <= 12 || (b <= 16 && pencils >= 4 * kTwoStepWidePencils) ? 64 : 32;
+}
 // The two-step kernel for length n, a number of pencils and the load and
 // store modes, or null.
 const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, int smode);

@@ -204,7 +204,10 @@ const KernelInfo* find_mixed_kernel(int64_t n, uint64_t code, int tile, int lmod
 const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, int smode) {
   if (!two_step_split(n)) return nullptr;
   int tile = two_step_tile(n);
-  if (tile == 16 && pencils <= 16 * (int64_t)two_step_idle_tiles(n)) tile = 8;
+  if (const int wide = two_step_wide_tile(n, pencils))
+    tile = wide;
+  else if (tile == 16 && pencils <= 16 * (int64_t)two_step_idle_tiles(n))
+    tile = 8;
   for (const KernelInfo& k : kernel_registry())
     if (k.two_step && k.mixed && k.fixed_n == n && k.tile == tile && k.lmode == lmode &&
         k.smode == smode)

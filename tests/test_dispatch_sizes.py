@@ -1,8 +1,10 @@
 """Which form of a pass large, misaligned and long shapes take, where the form
 measured fastest depends on more than the pass length."""
+import numpy as np
 import pytest
 
-from paper_1904_10119_amd import dft3d
+import oracle
+from paper_1904_10119_amd import dft3d, inputs
 
 
 def passes(shape, schedule="pencil", **kw):
@@ -19,3 +21,60 @@ def test_axes_of_2048_beside_other_lengths_keep_the_halves_kernel(shape):
         if n == 2048:
             assert p["halves"] and not p["mixed"], p["label"]
     assert all(" cyc" in p["label"] for p in passes((1024, 1000, 900)))
+
+
+SHORT = [48, 49, 56, 60, 72, 80, 90, 96, 98, 100, 104, 105, 112, 117, 120, 125, 126]
+
+
+@pytest.mark.parametrize("n", SHORT)
+def test_short_lengths_on_large_grids_take_wide_tiles(n):
+    """From 2^17 pencils up the two-step passes of 48..127 points take 32 or 64
+    pencils, in every order, so that row segments span several lines."""
+    b = passes((1, 1, n))[0]["split"][1]
+    for k, want in (((2040, 64), 16), ((2048, 64), 64 if b <= 12 else 32),
+                    ((2048, 256), 64 if b <= 16 else 32)):
+        for shape, schedule, at in ((k + (n,), "pencil", 0), (k + (n,), "slab", 0),
+                                    ((n,) + k, "slab", -1)):
+            p = passes(shape, schedule, fused_plane=0)[at]
+            assert p["split"] and p["pencils"] == k[0] * k[1]
+            assert p["tile"] == want, (shape, schedule, p["tile"], want)
+            assert p["threads"] <= 1024 and p["lds_bytes"] <= 160 * 1024
+    assert passes((2048, 2048, 45))[0]["tile"] == 16
+
+
+def bar(shape):
+    """log2(n) + 1 rounding levels an axis at the tol(N) rate of 1e-6 / 18 a level."""
+    return 1e-6 * sum(np.log2(n) + 1 for n in shape if n > 1) / 18.0
+
+
+def check_sampled(shape, schedule, seed):
+    """Sampled output pencils, the last of each axis among them, against the
+    oracle's direct sums, and the round trip."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = inputs.uniform_c64(shape, seed)
+    xt = torch.from_numpy(x).cuda()
+    y = dft3d.fftn(xt, schedule=schedule)
+    torch.cuda.synchronize()
+    g = np.random.default_rng(seed)
+    k0 = np.concatenate([[0, shape[0] - 1], g.integers(0, shape[0], 4)])
+    k1 = np.concatenate([[0, shape[1] - 1], g.integers(0, shape[1], 4)])
+    got = y[torch.from_numpy(k0).cuda(), torch.from_numpy(k1).cuda(), :].cpu().numpy()
+    assert oracle.rel_l2(got, oracle.sample_pencils(x, k0, k1, -1)) <= bar(shape)
+    back = dft3d.ifftn(y, schedule=schedule) / x.size
+    rt = (torch.linalg.vector_norm(back - xt) / torch.linalg.vector_norm(xt)).item()
+    assert rt <= 2 * bar(shape)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(363, 362, 60), (363, 96, 362), (105, 363, 362),
+                                   (363, 362, 125), (725, 112, 724), (48, 363, 362)])
+@pytest.mark.parametrize("schedule", ["pencil", "slab"])
+def test_wide_tiles_on_the_gpu(shape, schedule):
+    """Tiles of 64 and 32 pencils in every order, with a ragged last tile."""
+    print("case wide tiles", shape, schedule, flush=True)
+    short = min(shape)
+    assert any(p["pencils"] * short == np.prod(shape) and p["tile"] in (32, 64)
+               for p in passes(shape, schedule))
+    check_sampled(shape, schedule, 81)
