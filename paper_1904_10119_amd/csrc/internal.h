@@ -168,9 +168,24 @@ constexpr int two_step_wide_tile(int64_t n, int64_t pencils) {
   const int64_t b = n / two_step_split(n);
   return b <= 12 || (b <= 16 && pencils >= 4 * kTwoStepWidePencils) ? 64 : 32;
 }
-// The two-step kernel for length n, a number of pencils and the load and
-// store modes, or null.
-const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, int smode);
+// Tiles of 32 pencils of the rotating passes of 128 points and more whose rows
+// (as long as there are pencils) do not start on 128-byte lines, from 2^16
+// pencils up: a tile of 16 then writes two half lines a row, which two or more
+// workgroups a CU leave half-written in the L2.  Measured, staged pass / 16 /
+// 32 pencils, us: 192 of 701 x 192 x 703 273 / 350 / 272, 300 of 411 x 300 x 409 (at
+// 168099 pencils) 1 / 1.17 / 1.01 of the staged time, 384 1 / 1.24 / 0.99, 500 1 /
+// 1.19 / 0.90, 600 1 / 1.35 / 1.04; at 60501 pencils 384 1.07 / 1.10, 500 1.04 /
+// 1.01, 600 1.14 / 1.01, 375 0.76 / 0.83, and below that 16 are ahead.
+constexpr int64_t kTwoStepMisalignedPencils = int64_t(1) << 16;
+constexpr int two_step_misaligned_tile(int64_t n) {
+  if (n < 128 || !two_step_split(n) || two_step_tile(n) != 16) return 0;
+  const int64_t a = two_step_split(n), b = n / a;
+  return 32 * b <= 1024 && 32 * ((a * (b | 1)) | 1) * 8 <= 160 * 1024 ? 32 : 0;
+}
+// The two-step kernel for length n, a number of pencils, the load and store
+// modes and the stride between output points k, or null.
+const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, int smode,
+                                       int64_t oks);
 // Twiddles of a two-step pass: out[tm (n / a) + j] = w_n^{tm j}, from FP64.
 void make_two_step_twiddles(int64_t n, int a, float2* out);
 // The product of a radix code's stages.

@@ -343,7 +343,7 @@ struct Builder {
     const KernelInfo* k = nullptr;
     int64_t pencils = 1;
     for (int i = 0; i < nf; ++i) pencils *= f[i].count;
-    if (!asked && opt.tile <= 0) k = find_two_step_kernel(n, pencils, lmode, smode);
+    if (!asked && opt.tile <= 0) k = find_two_step_kernel(n, pencils, lmode, smode, oks);
     if (!k) k = find_mixed_kernel(n, code, opt.tile, lmode, smode);
     if (!k || !code) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;

@@ -201,11 +201,16 @@ const KernelInfo* find_mixed_kernel(int64_t n, uint64_t code, int tile, int lmod
   return best;
 }
 
-const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, int smode) {
+const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, int smode,
+                                       int64_t oks) {
   if (!two_step_split(n)) return nullptr;
   int tile = two_step_tile(n);
+  const bool misaligned =
+      lmode == MODE_ROW && smode == MODE_COL && oks == pencils && pencils % 16 != 0;
   if (const int wide = two_step_wide_tile(n, pencils))
     tile = wide;
+  else if (misaligned && pencils >= kTwoStepMisalignedPencils && two_step_misaligned_tile(n))
+    tile = two_step_misaligned_tile(n);
   else if (tile == 16 && pencils <= 16 * (int64_t)two_step_idle_tiles(n))
     tile = 8;
   for (const KernelInfo& k : kernel_registry())

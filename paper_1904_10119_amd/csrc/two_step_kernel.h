@@ -23,7 +23,8 @@
 // load latency below.  The tile is 16 pencils so that a COL row segment is
 // one 128-byte line: 400^3 takes 603 us so, 762 us in tiles of 8 pencils
 // (64-byte segments) and 629 us in tiles of 32 (fewer workgroups a CU);
-// two_step_tile says where 8 are taken, two_step_wide_tile where more than 16.
+// two_step_tile says where 8 are taken, two_step_wide_tile and
+// two_step_misaligned_tile where more than 16.
 // Against the staged pass (same orders, MI355X): 96^3 25.0 -> 17.9 us, 90^3
 // 30.4 -> 18.7, 150^3 62.9 -> 32.6, 252^3 209 -> 141 (5.4 TB/s a pass),
 // 324^3 462 -> 326, 540^3 2370 -> 1481, 900^3 10.3 -> 8.6 ms, 640^3 2.95 ->
@@ -229,6 +230,8 @@ void add_two_step_kernels(std::vector<KernelInfo>& v) {
     constexpr int W1 = two_step_wide_tile(LO, int64_t(1) << 40);
     if constexpr (W0 > 0) add_two_step_modes<A, B, W0>(v);
     if constexpr (W1 != W0) add_two_step_modes<A, B, W1>(v);
+    if constexpr (constexpr int M = two_step_misaligned_tile(LO); M > 0)
+      v.push_back(kernel_info_two_step<A, B, M, MODE_ROW, MODE_COL>());
   }
 }
 

@@ -67,6 +67,20 @@ def check_sampled(shape, schedule, seed):
     assert rt <= 2 * bar(shape)
 
 
+@pytest.mark.parametrize("n", [130, 144, 192, 240, 300, 375, 384, 500, 600, 625])
+def test_misaligned_rotation_takes_tiles_of_32(n):
+    """From 2^16 pencils up the rotating passes whose rows do not start on
+    128-byte lines take 32 pencils; aligned rows, fewer pencils and the orders
+    that keep the layout take 16 (or 8 on small grids)."""
+    def tile(shape, schedule="pencil", at=0):
+        p = passes(shape, schedule, fused_plane=0)[at]
+        assert p["mixed"] and p["lds_bytes"] <= 160 * 1024
+        return p["tile"]
+    assert tile((257, 257, n)) == 32 and tile((256, 256, n)) == 16
+    assert tile((257, 253, n)) == 16
+    assert tile((257, 257, n), "slab") == 16 and tile((n, 257, 257), "slab", -1) == 16
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", [(363, 362, 60), (363, 96, 362), (105, 363, 362),
                                    (363, 362, 125), (725, 112, 724), (48, 363, 362)])
@@ -78,3 +92,14 @@ def test_wide_tiles_on_the_gpu(shape, schedule):
     assert any(p["pencils"] * short == np.prod(shape) and p["tile"] in (32, 64)
                for p in passes(shape, schedule))
     check_sampled(shape, schedule, 81)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(257, 257, 130), (257, 192, 259), (375, 259, 257),
+                                   (257, 257, 625)])
+def test_misaligned_tiles_of_32_on_the_gpu(shape):
+    """Tiles of 32 pencils with rows off the 128-byte lines and a ragged last
+    tile."""
+    print("case misaligned tiles", shape, flush=True)
+    assert any(p["tile"] == 32 and p["split"] for p in passes(shape))
+    check_sampled(shape, "pencil", 82)
