@@ -109,7 +109,11 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 // 44.0, 512 (512^3) 1252 / 1216 (whole transform), 1024 (64 x 1024 x 1024)
 // 251 / 246 and 1024^3 10.49 / 10.26 ms (whole transform).
 // Tiles of 16 pencils, with these exceptions:
-//  - 64 from 2^22 points up 32 pencils (64 x 512 x 512 43.0 / 41.9);
+//  - 64 at 2^22 points 32 pencils (level with the pass kernel: 64 x 1024 x 64
+//    rows 12.0 / 12.0), above them the pass kernel in 64 pencils (1201 x 1201 x
+//    64 rotated 279 against 302 us, in layout 249 / 261, 1024 x 1024 x 64 rows 184
+//    / 193, 2048 x 1024 x 64 409 / 427; 64 x 512 x 512 is the best case for two
+//    steps, 43.0 / 41.9);
 //  - 128 from 2^23 points up the 32-pencil pass kernel (64 x 1024 x 128 rows
 //    29.3 against 33.0, 256 x 256 x 128 30.0 / 32.9; 512 x 512 x 128 rows
 //    95.8 against 101 us with two steps in 32 pencils, 104 in 16);
@@ -129,6 +133,7 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, int smode) {
   const int64_t points = pencils * n;
   int tile = 16;
+  if (n == 64 && points > (int64_t(1) << 22)) return nullptr;
   if (n == 64 && points >= (int64_t(1) << 22)) tile = 32;
   if (n == 128 && points >= (int64_t(1) << 23)) return nullptr;
   if (n == 256 && points > (int64_t(1) << 25)) tile = 32;

@@ -23,6 +23,15 @@ def test_axes_of_2048_beside_other_lengths_keep_the_halves_kernel(shape):
     assert all(" cyc" in p["label"] for p in passes((1024, 1000, 900)))
 
 
+@pytest.mark.parametrize("schedule", ["pencil", "slab"])
+def test_64_points_on_large_grids_take_the_pass_kernel(schedule):
+    """Above 2^22 points the 64-point rows take the pass kernel's tiles of 64
+    pencils."""
+    for k, split in (((1024, 64), [8, 8]), ((1024, 128), []), ((1201, 1201), [])):
+        p = passes(k + (64,), schedule, fused_plane=0)[0]
+        assert p["n"] == 64 and p["split"] == split and (split or p["tile"] == 64), (k, p)
+
+
 SHORT = [48, 49, 56, 60, 72, 80, 90, 96, 98, 100, 104, 105, 112, 117, 120, 125, 126]
 
 
