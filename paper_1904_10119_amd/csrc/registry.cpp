@@ -122,6 +122,10 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 //  - 16, 32 and 64 along strided axes from 2^21 points up the pass kernel,
 //    whose 256, 128 or 64 pencils are long row segments (16 x 512 x 512 depth
 //    11.8 against 12.7, 32 x 256 x 512 10.9 against 13.0);
+//  - 512 along strided axes from 2^23 points up, and from 2^23 to 2^24 in every
+//    order but rows, the pass kernel (512 x 64 x 256 depth 25.0 against 27.0,
+//    512 x 512 x 64 columns 45.3 / 48.7, 512 x 256 x 64 rotated 24.9 / 27.3; rows
+//    and the rotation from 2^24 points up are level or 3 % faster in two steps);
 //  - 16 and 32 from 2^25 points up the pass kernel in every order: the cycled
 //    pencil passes of such arrays read pencils a plane apart and write row
 //    segments of a tile's pencils (16 x 1024 x 2048 102 against 127, 32 x 1024
@@ -137,6 +141,9 @@ const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, 
   if (n == 64 && points >= (int64_t(1) << 22)) tile = 32;
   if (n == 128 && points >= (int64_t(1) << 23)) return nullptr;
   if (n == 256 && points > (int64_t(1) << 25)) tile = 32;
+  if (n == 512 && smode == MODE_COL && points >= (int64_t(1) << 23) &&
+      (lmode == MODE_COL || points < (int64_t(1) << 24)))
+    return nullptr;
   if (n <= 32 && points >= (int64_t(1) << 25)) return nullptr;
   if (n <= 64 && lmode == MODE_COL && points >= (int64_t(1) << 21)) return nullptr;
   if (n >= 256 && pencils <= 16 * 512) tile = 8;

@@ -32,6 +32,22 @@ def test_64_points_on_large_grids_take_the_pass_kernel(schedule):
         assert p["n"] == 64 and p["split"] == split and (split or p["tile"] == 64), (k, p)
 
 
+def test_512_points_on_middle_grids_take_the_pass_kernel():
+    """Strided axes of 512 from 2^23 points up, and the rotation from 2^23 to
+    2^24, take the pass kernel; rows and the larger rotations two steps."""
+    def split(shape, schedule, at):
+        p = passes(shape, schedule, fused_plane=0)[at]
+        assert p["n"] == 512
+        return p["split"]
+    assert split((512, 128, 64), "slab", -1) == [16, 32]      # 2^22
+    assert split((512, 256, 64), "slab", -1) == []            # 2^23
+    assert split((64, 512, 512), "slab", 1) == []             # 2^24
+    assert split((64, 512, 512), "slab", 0) == [16, 32]
+    assert split((64, 256, 512), "pencil", 0) == []           # 2^23, rotated
+    assert split((128, 256, 512), "pencil", 0) == [16, 32]    # 2^24
+    assert split((64, 256, 512), "slab", 0) == [16, 32]
+
+
 SHORT = [48, 49, 56, 60, 72, 80, 90, 96, 98, 100, 104, 105, 112, 117, 120, 125, 126]
 
 
