@@ -405,10 +405,13 @@ bool default_mfma_persistent(int n, int precision) {
 //   length 512:  8192 8.4 9.0 10.8 15.7 19.1  2048 6.1 6.7 10.5 14.3 22.1  4096 6.2 6.7 8.2 14.0 19.3
 //   length 1024: 8192 8.9 9.4 10.2 13.1 20.6  2048 6.9 7.9 11.4 16.2 26.9  4096 6.9 7.5 9.4 14.0 21.4
 // and at 2^24 8192 is ahead at every length (256^3 55.2 against 59.3 in 4096).
-// Passes of lengths up to 128 that keep the layout stop at 2^20 (slab 256 x 128
-// x 64 34.2 in 8192, 35.3 in 4096).
+// Passes that keep the layout stop at 2^20 (slab, whole transforms, 8192 / 4096:
+// 256 x 128 x 64 34.2 / 35.3, 16 x 512 x 256 33.2 / 34.9, 32 x 256 x 256 30.9 / 31.5;
+// at 2^20 16 x 256 x 256 is 10 % faster in 4096).  The other split precisions
+// take the same rule: over 26 grids of 2^12 to 2^22 points, lengths 16 to 1024
+// and both orders, bf16x9, fp16x3, bf16x1 and fp16x1 take 0.71 to 1.00 of the time in 8192.
 static int mfma_tile_points(int n, int64_t points, bool keeps) {
-  const int most = n == 1024 || (n <= 128 && keeps) ? 20 : n == 512 ? 21 : 22;
+  const int most = n == 1024 || keeps ? 20 : n == 512 ? 21 : 22;
   if (n > 1024 || points > (int64_t(1) << most)) return 0;
   if (n > 256 || points > (int64_t(1) << 19)) return 4096;
   return n == 256 ? 2048 : 1024;

@@ -48,6 +48,18 @@ def test_512_points_on_middle_grids_take_the_pass_kernel():
     assert split((64, 256, 512), "slab", 0) == [16, 32]
 
 
+@pytest.mark.parametrize("precision", ["bf16x6", "bf16x9", "fp16x3", "bf16x1", "fp16x1"])
+def test_split_passes_that_keep_the_layout_take_small_tiles_up_to_2_20(precision):
+    """Above 2^20 points the in-layout split-precision passes keep 8192-point
+    tiles; the rotating ones of 256 points take less up to 2^22."""
+    def points(shape, schedule):
+        return {p["n"]: p["tile"] * p["n"] for p in
+                passes(shape, schedule, precision=precision, fused_plane=0)}
+    assert points((16, 512, 256), "slab") == {256: 8192, 512: 8192, 16: 8192}
+    assert points((16, 256, 256), "slab") == {256: 4096, 16: 4096}
+    assert points((32, 256, 256), "pencil")[256] == 4096
+
+
 SHORT = [48, 49, 56, 60, 72, 80, 90, 96, 98, 100, 104, 105, 112, 117, 120, 125, 126]
 
 
