@@ -119,9 +119,15 @@ const KernelInfo* pick_kernel(int n, int64_t pencils, int lmode, int smode, int 
       if (const KernelInfo* k = find_two_step_power_kernel(n, pencils, lmode, smode)) return k;
     }
     // half the default pencils of the longest lengths where fewer than 256
-    // workgroups would leave CUs idle (2048 x 32 x 32: 14.5 us a pass)
+    // workgroups would leave CUs idle.  Measured, whole / half, us a pass: 2048
+    // columns in 8 / 4 pencils 13.4 / 11.8 at 256 pencils, 22.8 / 22.5 at 1024,
+    // rows 12.8 / 11.8 and 14.7 / 13.5; 4096 in 4 / 2 columns 16.5 / 15.2 at 64
+    // pencils, 20.1 / 19.6 at 384 but 25.7 / 27.3 at 512 (so half of it up to
+    // 128 workgroups), rows 13.2 / 12.2 and at 512 14.9 / 13.4, rotated 17.2 /
+    // 15.5.
     int tile = default_tile(n);
-    if (n >= 2048 && !pers && pencils < 256 * tile) tile /= 2;
+    const int fill = n == 4096 && lmode == MODE_COL ? 128 : 256;
+    if (n >= 2048 && !pers && pencils < fill * tile) tile /= 2;
     if (const KernelInfo* k = find_kernel(n, tile, lmode, smode, tw, pers, nt)) return k;
   }
   // any available tile for this length

@@ -60,6 +60,21 @@ def test_split_passes_that_keep_the_layout_take_small_tiles_up_to_2_20(precision
     assert points((32, 256, 256), "pencil")[256] == 4096
 
 
+def test_half_tiles_of_the_longest_lengths():
+    """2048 and 4096 points take half the pencils where workgroups are few:
+    fewer than 256, or 128 for columns of 4096."""
+    def tile(shape, schedule, **kw):
+        return next(p["tile"] for p in passes(shape, schedule, fused_plane=0, split_max=4096, **kw)
+                    if p["n"] == max(shape))
+    assert tile((4096, 16, 16), "slab") == 2
+    assert tile((4096, 16, 32), "slab") == 4
+    assert tile((16, 32, 4096), "slab") == 2
+    assert tile((4096, 16, 32), "pencil") == 2
+    assert tile((32, 32, 4096), "slab") == 4
+    assert tile((2048, 32, 32), "slab", halves=0) == 4
+    assert tile((2048, 64, 32), "slab", halves=0) == 8
+
+
 SHORT = [48, 49, 56, 60, 72, 80, 90, 96, 98, 100, 104, 105, 112, 117, 120, 125, 126]
 
 
