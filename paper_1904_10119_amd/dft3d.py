@@ -90,16 +90,18 @@ def lib():
     return L
 
 
-# torch's complex64, and its call for the raw handle of a device's current
+# torch's Size and complex64, and its call for the raw handle of a device's current
 # stream (0.1 us, where torch.cuda.current_stream(device).cuda_stream takes
 # 1.9: a transform of 32^3 points is launched in 7.5); set on first use.
+_Size = None
 _complex64 = None
 _current_raw_stream = None
 
 
 def _load_torch() -> None:
-    global _complex64, _current_raw_stream
+    global _Size, _complex64, _current_raw_stream
     import torch
+    _Size = torch.Size
     _current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     _complex64 = torch.complex64
 
@@ -338,7 +340,8 @@ _plans: Dict[Tuple, Plan] = {}
 def get_plan(shape, schedule="auto", precision="fp32", device_index=0, **opts) -> Plan:
     if "radices" in opts:
         opts["radices"] = radix_code(opts["radices"])
-    key = (tuple(shape), schedule, precision, device_index,
+    # (a Size holds ints; other sides count by value, whatever integer type)
+    key = (shape if type(shape) is _Size else tuple(map(int, shape)), schedule, precision, device_index,
            tuple(sorted(opts.items())) if opts else ())
     p = _plans.get(key)
     if p is None:
