@@ -288,6 +288,11 @@ int dft3d_plan_describe(int64_t n0, int64_t n1, int64_t n2, int schedule,
 int dft3d_plan_set_option(dft3d_plan_t plan, int key, int64_t value);
 int dft3d_plan_get_option(dft3d_plan_t plan, int key, int64_t* value);
 
+/* Successful dft3d_plan_set_option calls of the process so far, on any plan:
+ * a binding that keeps what it asked a plan for (its workspace size) asks
+ * again when this has moved. */
+extern volatile int64_t dft3d_option_epoch;
+
 /* Bytes of device workspace dft3d_execute needs (0 if none): the second
  * buffer a redistribution writes into when it cannot work in place (the
  * target B of eq. (12)); N * 8 bytes for the pencil and volumetric

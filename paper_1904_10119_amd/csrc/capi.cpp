@@ -400,6 +400,8 @@ int execute_passes(dft3d_plan_s* p, const void* in, void* out, int sign, hipStre
 
 extern "C" {
 
+volatile int64_t dft3d_option_epoch = 0;
+
 const char* dft3d_status_string(int status) {
   switch (status) {
     case DFT3D_OK: return "ok";
@@ -535,6 +537,7 @@ int dft3d_plan_set_option(dft3d_plan_t p, int key, int64_t value) {
   } else {
     destroy_twin(p);        // rebuilt from the new options on demand
     batch_forget_plan(p);   // batched descriptors of the old pass list
+    __atomic_fetch_add(&dft3d_option_epoch, 1, __ATOMIC_RELEASE);
   }
   return st;
 }

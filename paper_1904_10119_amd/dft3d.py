@@ -42,6 +42,7 @@ EXPORTS = ("dft3d_status_string", "dft3d_plan", "dft3d_plan_describe",
            "dft3d_execute_noalloc", "dft3d_batch_describe")
 
 _lib = None
+_epoch = None  # the library's count of option changes, any plan's, by any caller
 
 
 class Dft3dError(RuntimeError):
@@ -53,7 +54,7 @@ class Dft3dError(RuntimeError):
 
 def lib():
     """Load libdft3d.so (after torch, so that one HIP runtime serves both)."""
-    global _lib
+    global _lib, _epoch
     if _lib is not None:
         return _lib
     try:  # torch ships the HIP runtime the library must share
@@ -86,6 +87,7 @@ def lib():
                                        sz, ctypes.POINTER(sz)]
     for f in EXPORTS[1:]:
         getattr(L, f).restype = ci
+    _epoch = ctypes.c_int64.in_dll(L, "dft3d_option_epoch")
     _lib = L
     return L
 
@@ -205,7 +207,9 @@ class Plan:
                             ctypes.byref(h)), "dft3d_plan")
         self._h = h
         self._ws = None
-        self._need = None  # workspace bytes of the current options, once asked for
+        # the library's count of option changes at which the bound workspace
+        # was last seen to suffice
+        self._bound_at = None
         try:
             if precision != "fp32":
                 self.set_option(OPT_PRECISION, PRECISIONS[precision])
@@ -250,7 +254,6 @@ class Plan:
         return self._h
 
     def set_option(self, key: int, value: int) -> None:
-        self._need = None
         _check(lib().dft3d_plan_set_option(self._h, key, int(value)), "set_option")
 
     def get_option(self, key: int) -> int:
@@ -270,12 +273,13 @@ class Plan:
 
     def bind_workspace(self, device) -> None:
         import torch
-        need = self._need = self.workspace_size()
-        if need == 0 or (self._ws is not None and self._ws.numel() >= need):
-            return
-        self._ws = torch.empty(need, dtype=torch.uint8, device=device)
-        _check(lib().dft3d_set_workspace(self._h, self._ws.data_ptr(), need),
-               "set_workspace")
+        epoch = _epoch.value  # read before the size it goes with
+        need = self.workspace_size()
+        if need > 0 and (self._ws is None or self._ws.numel() < need):
+            self._ws = torch.empty(need, dtype=torch.uint8, device=device)
+            _check(lib().dft3d_set_workspace(self._h, self._ws.data_ptr(), need),
+                   "set_workspace")
+        self._bound_at = epoch
 
     def _check_tensors(self, x, out) -> None:
         for t in (x, out):
@@ -284,28 +288,16 @@ class Plan:
             if t.shape != self.shape:
                 raise ValueError(f"shape {tuple(t.shape)} != plan {self.shape}")
 
-    def _bound(self) -> bool:
-        """Whether a workspace large enough for the plan's options is bound.  An
-        option set through the C ABI behind this object either shows up as
-        ERR_WORKSPACE_TOO_SMALL, before anything is enqueued, or, for a plan
-        that needed none, makes the library allocate the plan's own."""
-        need = self._need
-        return need is not None and (need == 0 or (self._ws is not None
-                                                   and self._ws.numel() >= need))
-
     def execute(self, x, out, inverse: bool = False, stream=None) -> None:
         """x, out: contiguous complex64 CUDA tensors of the plan's shape."""
         L = _lib or lib()
         if _complex64 is None:
             _load_torch()
         self._check_tensors(x, out)
-        if not self._bound():
+        if self._bound_at != _epoch.value:
             self.bind_workspace(x.device)
         s = _raw_stream(x.device) if stream is None else stream.cuda_stream
         st = L.dft3d_execute(self._h, x.data_ptr(), out.data_ptr(), 1 if inverse else -1, s)
-        if st == ERR_WORKSPACE_TOO_SMALL:
-            self.bind_workspace(x.device)
-            st = L.dft3d_execute(self._h, x.data_ptr(), out.data_ptr(), 1 if inverse else -1, s)
         if st != OK:
             raise Dft3dError(st, "dft3d_execute")
 
@@ -420,7 +412,7 @@ def fftn_batched(xs: List, inverse: bool = False, outs: Optional[List] = None,
     plans = [get_plan(x.shape, schedule, "fp32", x.device.index or 0,
                       **({"batch_launch": bl} if bl else {})) for x in xs]
     for p, x in zip(plans, xs):
-        if not p._bound():
+        if p._bound_at != _epoch.value:
             p.bind_workspace(x.device)
     arr = ctypes.c_void_p * max(n, 1)
     hp = arr(*[p._h.value for p in plans])
