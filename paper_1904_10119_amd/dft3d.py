@@ -112,9 +112,9 @@ def _raw_stream(device) -> int:
     """The current stream of a CUDA tensor's device."""
     if _complex64 is None:
         _load_torch()
-    if _current_raw_stream is not None:
+    if _current_raw_stream is not None and device.index is not None:
         return _current_raw_stream(device.index)
-    import torch
+    import torch  # also says what is wrong with a device that has no streams
     return torch.cuda.current_stream(device).cuda_stream
 
 

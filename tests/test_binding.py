@@ -148,3 +148,14 @@ def test_workspace_size_is_asked_once_per_option_change(library, monkeypatch):
     for _ in range(5):
         p.execute(x, x)
     assert len(asked) == 2
+
+
+def test_a_device_without_streams_is_refused_by_torch(monkeypatch):
+    """CPU tensors in a batched call end in torch's ValueError, as from
+    torch.cuda.current_stream."""
+    def refuse(device):
+        raise ValueError(f"Expected a cuda device, but got: {device}")
+    dft3d._load_torch()
+    monkeypatch.setattr(torch.cuda, "current_stream", refuse)
+    with pytest.raises(ValueError, match="cuda device"):
+        dft3d._raw_stream(torch.device("cpu"))
