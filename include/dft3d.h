@@ -98,10 +98,16 @@ enum dft3d_status {
  * an option rebuilds the pass list (host work plus a table upload). */
 enum dft3d_option {
   DFT3D_OPT_PRECISION = 1,   /* enum dft3d_precision; default FP32 */
-  DFT3D_OPT_TILE = 2,        /* pencils per workgroup, power of two; 0 = default
-                                (Bluestein passes up to 1024 points and
-                                split-precision passes have one tile per
-                                length, or size of grid, and ignore it) */
+  DFT3D_OPT_TILE = 2,        /* pencils per workgroup, power of two; 0 = default.
+                                A pass whose length has no kernel of that
+                                tile keeps its default; other kernels of
+                                the length may be slower ones than the
+                                default's (Bluestein passes up to 1024
+                                points: power-of-two FFTs).  In
+                                split-precision passes any tile > 0 turns
+                                the small tiles of small grids off, and
+                                one equal to the wide form's (length 2048
+                                rotated on write: 16) selects it */
   DFT3D_OPT_XCD_REMAP = 3,   /* 1 = map consecutive tiles to one XCD; default 1 */
   DFT3D_OPT_SPLIT_MAX = 4,   /* longest axis done in one pass; longer axes
                                 are split four-step; 0 = default */

@@ -1,6 +1,7 @@
-// Lengths above 1024 that are not smooth: the DFT of length n as a circular
-// convolution of length m (a power of two, m >= 2n - 1) computed with two
-// power-of-two FFTs (Bluestein's chirp-z identity).  With the chirp
+// Lengths above 1024 that are not smooth (and shorter ones in tiles asked
+// for): the DFT of length n as a circular convolution of length m (a power of
+// two, m >= 2n - 1) computed with two power-of-two FFTs (Bluestein's chirp-z
+// identity).  With the chirp
 // w[j] = exp(-pi i j^2 / n) and jk = (j^2 + k^2 - (k - j)^2) / 2,
 //   y[k] = w[k] sum_j (x[j] w[j]) conj(w[k - j]),
 // a circular convolution of the padded a[j] = x[j] w[j] (zero for j >= n)

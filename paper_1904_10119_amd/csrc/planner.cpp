@@ -290,9 +290,13 @@ struct Builder {
   // pencils of fields f (bluestein.h documents the argument fields).
   void add_bluestein(int64_t n, const Field* f, int nf, int64_t ijs, int64_t oks,
                      const std::string& what, int lmode = MODE_ROW, int smode = MODE_COL) {
-    // two-step FFTs up to n = 1024, power-of-two ones above
+    // two-step FFTs up to n = 1024, power-of-two ones above and for an
+    // asked-for tile that only they have
     const KernelInfo* k = find_bluestein_two_step_kernel(n, lmode, smode);
-    if (!k) k = find_bluestein_kernel((int)bluestein_length(n), opt.tile);
+    if (!k || (opt.tile > 0 && opt.tile != k->tile)) {
+      const KernelInfo* power = find_bluestein_kernel((int)bluestein_length(n), opt.tile);
+      if (!k || (power && power->tile == opt.tile)) k = power;
+    }
     const std::string label = what + " via " + std::to_string(k ? k->n : 0);
     if (!k) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;
