@@ -92,8 +92,14 @@ const KernelInfo* find_move_only_kernel(const KernelInfo* k, int mode);
 const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_twiddle,
                               int persistent, int nontemporal);
 // The two-step kernel (two_step_kernel.h) for an FP32 pass of a power of two
-// over `pencils` pencils, or null.
-const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, int smode);
+// over `pencils` pencils with output points oks apart, or null.
+const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, int smode,
+                                             int64_t oks);
+// Whether a rotating pass writes rows (as long as there are pencils) that do
+// not start on 128-byte lines.
+inline bool rows_off_lines(int64_t pencils, int lmode, int smode, int64_t oks) {
+  return lmode == MODE_ROW && smode == MODE_COL && oks == pencils && pencils % 16 != 0;
+}
 // The two-halves pass of length n (halves_kernel.h) with the given load and
 // store orders and form, or null if none is compiled.
 const KernelInfo* find_halves_kernel(int n, int lmode, int smode, int persistent,

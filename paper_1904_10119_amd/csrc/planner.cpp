@@ -71,7 +71,7 @@ constexpr int64_t kGroupBytes = int64_t(256) << 20;
 // one-tile-per-workgroup kernels with ordinary ones.  Automatic mode uses
 // the persistent form with streaming accesses for arrays that cannot stay
 // in the caches, and the one-tile form with ordinary accesses otherwise.
-const KernelInfo* pick_kernel(int n, int64_t pencils, int lmode, int smode, int tw,
+const KernelInfo* pick_kernel(int n, int64_t pencils, int lmode, int smode, int64_t oks, int tw,
                               const Options& opt, int64_t total_points) {
   struct Choice {
     int pers, nt;
@@ -116,7 +116,8 @@ const KernelInfo* pick_kernel(int n, int64_t pencils, int lmode, int smode, int 
     if (opt.tile > 0) {
       if (const KernelInfo* k = find_kernel(n, opt.tile, lmode, smode, tw, pers, nt)) return k;
     } else if (!pers && !nt && !tw) {
-      if (const KernelInfo* k = find_two_step_power_kernel(n, pencils, lmode, smode)) return k;
+      if (const KernelInfo* k = find_two_step_power_kernel(n, pencils, lmode, smode, oks))
+        return k;
     }
     // half the default pencils of the longest lengths where fewer than 256
     // workgroups would leave CUs idle.  Measured, whole / half, us a pass: 2048
@@ -245,7 +246,7 @@ struct Builder {
         k = find_mfma_kernel(n, pencils, lmode, smode, opt.precision, pers, 0, opt.tile);
       if (k) leaf = opt.precision;
     }
-    if (!k) k = pick_kernel(n, pencils, lmode, smode, tw, opt, total_points);
+    if (!k) k = pick_kernel(n, pencils, lmode, smode, oks, tw, opt, total_points);
     if (!k) {
       status = DFT3D_ERR_UNSUPPORTED_SIZE;
       return;

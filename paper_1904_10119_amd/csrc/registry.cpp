@@ -122,6 +122,10 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 //  - 16, 32 and 64 along strided axes from 2^21 points up the pass kernel,
 //    whose 256, 128 or 64 pencils are long row segments (16 x 512 x 512 depth
 //    11.8 against 12.7, 32 x 256 x 512 10.9 against 13.0);
+//  - 64 from 2^20 points and 256 from 2^24, where rotated rows do not start on
+//    lines, the pass kernel's 64 and 32 pencils (251 x 64 x 251 11.7 against 12.7,
+//    255 x 256 x 511 109 / 124; below 127 x 64 x 129 8.1 / 7.1, 127 x 256 x 129
+//    13.1 / 13.3; 128 and 512 are level or ahead in two steps);
 //  - 512 along strided axes from 2^23 points up, and from 2^23 to 2^24 in every
 //    order but rows, the pass kernel (512 x 64 x 256 depth 25.0 against 27.0,
 //    512 x 512 x 64 columns 45.3 / 48.7, 512 x 256 x 64 rotated 24.9 / 27.3; rows
@@ -134,8 +138,12 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 //    (16 x 256 x 256 8.3 / 7.2, 16 x 64 x 1024 12.2 / 9.1, 16 x 512 x 512 rows
 //    15.3 / 14.2; tiles of 4 gain no more, and at 1024 tiles 16 are faster:
 //    32 x 512 x 512 rows 32.4 against 34.7).
-const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, int smode) {
+const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, int smode,
+                                             int64_t oks) {
   const int64_t points = pencils * n;
+  if (rows_off_lines(pencils, lmode, smode, oks) &&
+      ((n == 64 && points >= (int64_t(1) << 20)) || (n == 256 && points >= (int64_t(1) << 24))))
+    return nullptr;
   int tile = 16;
   if (n == 64 && points > (int64_t(1) << 22)) return nullptr;
   if (n == 64 && points >= (int64_t(1) << 22)) tile = 32;
@@ -217,8 +225,7 @@ const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, in
                                        int64_t oks) {
   if (!two_step_split(n)) return nullptr;
   int tile = two_step_tile(n);
-  const bool misaligned =
-      lmode == MODE_ROW && smode == MODE_COL && oks == pencils && pencils % 16 != 0;
+  const bool misaligned = rows_off_lines(pencils, lmode, smode, oks);
   if (const int wide = two_step_wide_tile(n, pencils))
     tile = wide;
   else if (misaligned && pencils >= kTwoStepMisalignedPencils && two_step_misaligned_tile(n))

@@ -75,6 +75,16 @@ def test_half_tiles_of_the_longest_lengths():
     assert tile((2048, 64, 32), "slab", halves=0) == 8
 
 
+def test_misaligned_rotation_of_powers_of_two():
+    """Rotating passes of 64 and 256 points whose rows do not start on 128-byte
+    lines take the pass kernel's longer tiles on large grids."""
+    def split(shape):
+        return next(bool(p["split"]) for p in passes(shape) if p["n"] in (64, 256))
+    assert not split((251, 64, 251)) and split((127, 64, 129)) and split((256, 64, 250))
+    assert not split((255, 256, 511)) and split((127, 256, 129)) and split((256, 256, 500))
+    assert passes((251, 251, 64), "slab")[0]["split"] == [8, 8]
+
+
 SHORT = [48, 49, 56, 60, 72, 80, 90, 96, 98, 100, 104, 105, 112, 117, 120, 125, 126]
 
 
