@@ -78,8 +78,7 @@ struct KernelInfo {
   int mfma_leaf = 0;  // split-precision MFMA passes: the leaf length (16 or 32)
   int rader = 0;      // > 0: Rader pass for prime lengths up to n - 1 (variant as mixed)
   int mfma_wide = 0;  // MFMA one-tile pass: 1 with twice the default tile, -1 with less than it
-  int two_step = 0;   // > 0: mixed-radix pass in two register steps (two_step_kernel.h);
-                      // the first step of a compiled length, 1 for any length
+  int two_step = 0;   // > 0: pass in two register steps (two_step_kernel.h), its first step
   int halves = 0;     // 1: rotate-on-write pass of length n as two half-length
                       // transforms after a radix-2 split (halves_kernel.h)
 };

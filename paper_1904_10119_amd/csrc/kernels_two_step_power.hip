@@ -7,7 +7,9 @@ void register_kernels_two_step_power(std::vector<KernelInfo>& v) {
   add_two_step_powers<16, 16>(v);
   add_two_step_powers<32, 16>(v);
   add_two_step_powers<64, 16>(v);
-  add_two_step_powers<64, 32>(v);
+  // (columns of 64 points leave for the pass kernel below 2^22 points)
+  add_two_step_power<64, 32, MODE_ROW, MODE_COL>(v);
+  add_two_step_power<64, 32, MODE_ROW, MODE_ROW>(v);
   add_two_step_powers<128, 16>(v);
   add_two_step_powers<256, 16>(v);
   add_two_step_powers<256, 8>(v);

@@ -156,8 +156,8 @@ const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, 
   if (n <= 64 && lmode == MODE_COL && points >= (int64_t(1) << 21)) return nullptr;
   if (n >= 256 && pencils <= 16 * 512) tile = 8;
   for (const KernelInfo& k : kernel_registry())
-    if (k.two_step && !k.mixed && !k.bluestein && !k.move_only && k.n == n && k.tile == tile &&
-        k.lmode == lmode && k.smode == smode)
+    if (k.two_step && !k.mixed && !k.bluestein && !k.rader && !k.move_only && k.n == n &&
+        k.tile == tile && k.lmode == lmode && k.smode == smode)
       return &k;
   return nullptr;
 }
