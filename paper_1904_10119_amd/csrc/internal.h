@@ -156,6 +156,14 @@ constexpr int two_step_tile(int64_t n) {
 // 26.5 / 21.8; 1000 36 tiles 9.7 / 7.9, 270 tiles 21.3 / 18.0; 150 and below
 // equal (4 pencils gain no more: 375 4.7, 585 25.4, 1000 18.1).
 constexpr int two_step_idle_tiles(int64_t n) { return n < 360 ? 0 : n < 512 ? 256 : 544; }
+// The same where rotated rows do not start on 128-byte lines: from 640 points
+// up 8 pencils stay ahead to 1344 tiles (staged / 16 / 8 pencils, us: 640 at
+// 12543 pencils 31.0 / 35.1 / 29.0, at 20503 48.0 / 51.5 / 46.7, 896 at 20503 61.2 /
+// 65.9 / 61.4, 1000 73.4 / 75.8 / 69.2; at 39713 640 1.12 / 1.10 and 800 1.00 / 1.09
+// of the staged time).
+constexpr int two_step_idle_tiles_off_lines(int64_t n) {
+  return n < 640 ? two_step_idle_tiles(n) : 1344;
+}
 // Tiles of 64 or 32 pencils of the lengths 48..127 on large grids, where tiles
 // of 16 write and read row segments of only one line: from 2^17 pencils up 64
 // pencils where the second factor is at most 12 (a workgroup of at most 768

@@ -230,7 +230,8 @@ const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, in
     tile = wide;
   else if (misaligned && pencils >= kTwoStepMisalignedPencils && two_step_misaligned_tile(n))
     tile = two_step_misaligned_tile(n);
-  else if (tile == 16 && pencils <= 16 * (int64_t)two_step_idle_tiles(n))
+  else if (tile == 16 && pencils <= 16 * (int64_t)(misaligned ? two_step_idle_tiles_off_lines(n)
+                                                             : two_step_idle_tiles(n)))
     tile = 8;
   for (const KernelInfo& k : kernel_registry())
     if (k.two_step && k.mixed && k.fixed_n == n && k.tile == tile && k.lmode == lmode &&

@@ -104,6 +104,16 @@ def test_short_lengths_on_large_grids_take_wide_tiles(n):
     assert passes((2048, 2048, 45))[0]["tile"] == 16
 
 
+@pytest.mark.parametrize("n", [640, 768, 896, 1000])
+def test_long_misaligned_rotations_on_small_grids_take_tiles_of_8(n):
+    """From 640 points up 8 pencils, to 1344 tiles of 16 where rotated rows do
+    not start on 128-byte lines, to 544 where they do."""
+    def tile(a, b):
+        return passes((a, b, n))[0]["tile"]
+    assert tile(101, 203) == 8 and tile(151, 263) == 16
+    assert tile(104, 200) == 16 and tile(64, 136) == 8
+
+
 def bar(shape):
     """log2(n) + 1 rounding levels an axis at the tol(N) rate of 1e-6 / 18 a level."""
     return 1e-6 * sum(np.log2(n) + 1 for n in shape if n > 1) / 18.0
