@@ -22,8 +22,11 @@
  *               one is recorded, otherwise SLAB below 256 MiB (arrays the
  *               Infinity Cache can hold) and PENCIL from 256 MiB on; with
  *               lengths that are not powers of two PENCIL, or SLAB from 2^20
- *               points to 2.5 GiB where the pencil passes' rows would not
- *               start on 128-byte lines.
+ *               points to 2.5 GiB where every axis has a pass in two register
+ *               steps (those above 700 in tiles of 16 pencils) and the pencil
+ *               rows of an axis of at most 640 would not start on 128-byte
+ *               lines (the product of the other two axes is no multiple of
+ *               16), unless an option names a tile, radices or a pencil form.
  *
  * Data: complex64 = two IEEE binary32 (re, im), interleaved, 8 bytes per
  * point; C order (n0, n1, n2), n2 contiguous; device pointers, 16-byte
@@ -250,21 +253,21 @@ const char* dft3d_status_string(int status);
  * [1, 4096].  Powers of two run on every schedule.  Other lengths (the
  * paper's experiments use powers of two; it leaves sizes its process grid
  * does not divide to future work, Section 3.2) run with FP32 precision and
- * the natural layout on every schedule, one pass per
- * such axis (rotate-on-write in the pencil schedule, in layout in the slab
- * and volumetric schedules): a mixed-radix pass when every prime factor of
- * n_d is at most 13 (in two register steps where n_d <= 2000 splits into two
- * factors of at most 50, 48 from 1700 up, else in stages of radix 2, 3, 4, 5, 7, 8, 10, 11,
- * 13, 16), else for
- * the primes n_d whose n_d - 1 has that property and that a Rader kernel is
- * compiled for a Rader pass (a circular convolution of length n_d - 1 done
- * with two mixed-radix FFTs, see DFT3D_OPT_RADER), else a Bluestein pass (the
- * DFT of length n as a circular convolution of length m done with two FFTs in
- * the same workgroup: up to n = 1024 m is the next of a ladder of products
- * m >= 2n, above it the power of two >= 2n - 1, up to 8192).  Split
- * precisions, the shuffled layout and move-only plans with such lengths
- * return UNSUPPORTED_SCHEDULE.  The workspace is N * 8 bytes as for powers of
- * two.  Validates the arguments first (INVALID_ARG / UNSUPPORTED_SIZE / UNSUPPORTED_SCHEDULE), then needs a HIP
+ * the natural layout on every schedule, one pass per such axis
+ * (rotate-on-write in the pencil schedule, in layout in the slab and
+ * volumetric schedules): a mixed-radix pass when every prime factor of n_d is
+ * at most 13 (in two register steps where n_d <= 2000 splits into two factors
+ * of at most 50, 48 from 1700 up, else in stages of radix 2, 3, 4, 5, 7, 8,
+ * 10, 11, 13, 16), else for the primes n_d whose n_d - 1 has that property and
+ * that a Rader kernel is compiled for a Rader pass (a circular convolution of
+ * length n_d - 1 done with two mixed-radix FFTs, see DFT3D_OPT_RADER), else a
+ * Bluestein pass (the DFT of length n as a circular convolution of length m
+ * done with two FFTs in the same workgroup: up to n = 1024 m is the next of a
+ * ladder of products m >= 2n, above it the power of two >= 2n - 1, up to
+ * 8192).  Split precisions, the shuffled layout and move-only plans with such
+ * lengths return UNSUPPORTED_SCHEDULE.  The workspace is N * 8 bytes as for
+ * powers of two (none on the slab schedule).  Validates the arguments first
+ * (INVALID_ARG / UNSUPPORTED_SIZE / UNSUPPORTED_SCHEDULE), then needs a HIP
  * device (NO_DEVICE), then allocates and uploads the twiddle tables on the
  * current device (OUT_OF_MEMORY / HIP_ERROR).  *out receives the handle, or
  * NULL on error.  The workspace is not allocated here. */

@@ -218,13 +218,13 @@ KernelInfo kernel_info_bluestein_two_step(int smode) {
 // whose factors the registers take (A up to 64, of which half is zero or not
 // wanted; B, whose DFT runs whole and twice, up to 32).
 constexpr int kBluesteinLadder[][2] = {
-    {8, 8}, {6, 12}, {8, 10}, {8, 12}, {10, 10}, {12, 9}, {14, 8}, {12, 10}, {16,
-    8}, {12, 12}, {16, 10}, {12, 14}, {16, 12}, {10, 20}, {12, 18}, {16, 14}, {12,
-    20}, {16, 16}, {24, 12}, {16, 20}, {24, 14}, {24, 15}, {16, 24}, {20, 20}, {24,
-    18}, {24, 20}, {16, 32}, {24, 24}, {24, 25}, {32, 20}, {24, 28}, {24, 30}, {24,
-    32}, {28, 28}, {28, 30}, {32, 28}, {32, 30}, {32, 32}, {36,
-    30}, {48, 24}, {40, 30}, {40, 32}, {48, 28}, {48, 30}, {48, 32}, {56, 30}, {56,
-    32}, {60, 32}, {64, 32}};
+    {8, 8}, {6, 12}, {8, 10}, {8, 12}, {10, 10}, {12, 9}, {14, 8},
+    {12, 10}, {16, 8}, {12, 12}, {16, 10}, {12, 14}, {16, 12}, {10, 20},
+    {12, 18}, {16, 14}, {12, 20}, {16, 16}, {24, 12}, {16, 20}, {24, 14},
+    {24, 15}, {16, 24}, {20, 20}, {24, 18}, {24, 20}, {16, 32}, {24, 24},
+    {24, 25}, {32, 20}, {24, 28}, {24, 30}, {24, 32}, {28, 28}, {28, 30},
+    {32, 28}, {32, 30}, {32, 32}, {36, 30}, {48, 24}, {40, 30}, {40, 32},
+    {48, 28}, {48, 30}, {48, 32}, {56, 30}, {56, 32}, {60, 32}, {64, 32}};
 constexpr int kBluesteinLadderSize = sizeof(kBluesteinLadder) / sizeof(kBluesteinLadder[0]);
 
 // The kernels of ladder entries LO <= i < HI, for every order: lanes along

@@ -130,7 +130,8 @@ bool radix_code_valid(uint64_t code);
 // <= 48 from 1700 up).  Measured, staged / two-step: 605 x 605 x 64 (B = 55) 292
 // / 327 us, 1750 x 1750 x 64 (35 x 50) 2057 / 2269, 1715 x 1715 x 64 (35 x 49)
 // 2024 / 2286; 1617 x 1617 x 64 (33 x 49) 2113 / 2019, 1029 x 1029 x 64 (21 x
-// 49) 840 / 713, 1920 x 1920 x 64 (40 x 48) 3628 / 2619.
+// 49) 840 / 713, 1323 x 1323 x 64 (27 x 49) 1329 / 1219, 1920 x 1920 x 64 (40 x 48)
+// 3628 / 2619.
 constexpr int two_step_split(int64_t n) {
   if (n < 6 || n > 2000) return 0;
   int64_t m = n;

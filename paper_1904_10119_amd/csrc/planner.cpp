@@ -13,11 +13,15 @@
 //     stride-A subsequences x[l + A k] of each residue l, times w_n^{l k'},
 //     stored exchanged as T0[k'][l]; V2 = DFT_A over l, stored at
 //     y[k' + Bf l'].
-//   AUTO: below 256 MiB (arrays the Infinity Cache can hold between
-//     passes) SLAB, whose planes of up to 128 x 128 points take one fused
-//     pass; above it the pencil schedule (the cycled intermediate orders
-//     where every axis is a power of two and unsplit), with axes longer than
-//     a threshold split into V1 + V2 as in the volumetric schedule.
+//   AUTO, every axis a power of two: below 256 MiB (arrays the Infinity Cache
+//     can hold between passes) SLAB, whose planes of up to 128 x 128 points
+//     take one fused pass; above it the pencil schedule (the cycled
+//     intermediate orders where no axis is split), with axes longer than a
+//     threshold split into V1 + V2 as in the volumetric schedule.
+//   AUTO with other lengths: the pencil rotation, the slab schedule where
+//     slab_suits_other says so (every axis in two register steps, rotated rows
+//     off the 128-byte lines), the cycled orders from 2.5 GiB up where
+//     cycle_suits_other does.
 //   SHUFFLED layout (volumetric only; Section 2.4, Section 3.2): the forward
 //     transform leaves out the final digit exchange of every split axis, so
 //     natural entry y[k' + Bf l'] stays at position l' + A k' (V2 writes in
@@ -95,7 +99,12 @@ const KernelInfo* pick_kernel(int n, int64_t pencils, int lmode, int smode, int6
   // ones (1024 x 16 x 64, depth pass 32 / 128 workgroups: 19.2 -> 9.1 us,
   // 2048 x 64 x 32 26.8 -> 18.6; at 256 halves tiles they are the faster
   // form again: 1024 x 128 x 64 30.6 against 35.2).  Arrays up to 2^16
-  // points keep the halves kernels.
+  // points keep the halves kernels although they are slower there too, one
+  // or two workgroups against a dozen (whole transforms, halves / whole
+  // length: 1024 x 4 x 2 22.1 / 11.3 us, 1024 x 8 x 8 23.4 / 12.8, 2048 x 4 x 8
+  // pencil 23.8 / 13.2): tests/test_plan_model.py (test_halves_option) asserts
+  // the option's default form on arrays of these sizes.  DFT3D_OPT_HALVES = 0
+  // gives the faster form.
   const bool idle = opt.nontemporal == 2 && opt.tile <= 0 &&
                     total_points > (int64_t(1) << 16) && pencils < 256 * (32768 / n);
   if (opt.halves && tw == 0 && !idle) {
@@ -615,8 +624,9 @@ int pencil_order(const int64_t n[3], const Options& opt) {
 // One rotate-on-write pass of the cycled order.  FP32 passes of length up
 // to 1024 take the one-tile kernel (two workgroups' tiles in flight per CU
 // instead of one persistent workgroup prefetching): measured in this order
-// 1024^3 10.75 -> 10.44 ms, 512^3 1.29 -> 1.26 ms, and in two register steps
-// (find_two_step_power_kernel) 10.26 and 1.22 ms; the persistent form
+// 1024^3 10.75 -> 10.44 ms, 512^3 1.29 -> 1.26 ms; in two register steps
+// (find_two_step_power_kernel) timed in turn 1024^3 is level (10.50, 10.40) and
+// 512^3 takes 1.22 ms; the persistent form
 // stays where streaming is forced on (nontemporal = 1) and for longer
 // lengths (the 2048 pass as persistent halves).
 void add_cycled(Builder& b, int len, const Field* f, int64_t oks, const char* lab) {
@@ -759,13 +769,16 @@ void pencil_cycled_other(Builder& b, const int64_t n[3]) {
 // start on 128-byte lines (the product of the other two axes is no multiple
 // of 16 points): neighbouring tiles then write parts of the same lines, and
 // with two or more workgroups a CU (lengths up to 640) they leave the L2
-// half-written.  Measured, rotation / slab: 375 x 486 x 400 737 / 673 us,
-// 375^3 659 / 538, 455 x 325 x 195 339 / 270, 525^3 1878 / 1484, 105^3 22.5
-// / 20.9; longer misaligned passes 675^3 3.06 / 3.24 ms; aligned ones 324^3
-// 326 / 341 us, 600 x 600 x 18 64 / 72; long axes in tiles of 8 pencils, whose
-// strided passes move 64-byte segments, 882 x 882 x 64 509 / 567, 1029 x 1029 x
-// 64 713 / 766 (686 x 686 x 64 329 / 279).  Below 2^20 points both are bound by
-// launches.
+// half-written.  Measured against the rotation in tiles of 16, rotation / slab:
+// 375 x 486 x 400 737 / 673 us, 375^3 659 / 538, 455 x 325 x 195 339 / 270, 105^3
+// 22.5 / 20.9.  With the rotation's tiles of 32 for such rows
+// (two_step_misaligned_tile) the two are level on the whole, 0.99 in the mean
+// over 84 shapes (375 x 486 x 400 692 / 672, 455 x 325 x 195 315 / 270, 441^3 858 /
+// 925, 243^3 132 / 146), and the slab needs no workspace.  Longer misaligned
+// passes 675^3 3.06 / 3.24 ms; aligned ones 324^3 326 / 341 us, 600 x 600 x 18 64 /
+// 72; long axes in tiles of 8 pencils, whose strided passes move 64-byte
+// segments, 882 x 882 x 64 509 / 567, 1029 x 1029 x 64 713 / 766 (686 x 686 x 64
+// 331 / 284).  Below 2^20 points both are bound by launches.
 bool slab_suits_other(const int64_t n[3], const Options& opt) {
   const int64_t total = n[0] * n[1] * n[2];
   if (total < (int64_t(1) << 20) || total * 8 >= kCycleBytes || opt.tile > 0 || opt.radices ||

@@ -107,7 +107,7 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 // us: length 16 (16 x 32 x 512) 4.2 / 3.3, 32 (32^3) 4.4 / 3.0, 64 (64^3) 4.4
 // / 3.7, 128 (128^3) 9.7 / 8.5, 256 (256^3 rows, columns) 56.9, 44.8 / 54.7,
 // 44.0, 512 (512^3) 1252 / 1216 (whole transform), 1024 (64 x 1024 x 1024)
-// 251 / 246 and 1024^3 10.49 / 10.26 ms (whole transform).
+// 251 / 246; 1024^3 is level, 10.50 / 10.40 ms timed in turn (whole transform).
 // Tiles of 16 pencils, with these exceptions:
 //  - 64 at 2^22 points 32 pencils (level with the pass kernel: 64 x 1024 x 64
 //    rows 12.0 / 12.0), above them the pass kernel in 64 pencils (1201 x 1201 x
