@@ -85,6 +85,13 @@ struct KernelInfo {
 
 // All compiled pass kernels.
 const std::vector<KernelInfo>& kernel_registry();
+// Its kernels of pass, convolution or bound length n that are not compiled for
+// one length, those compiled for length n alone, and the mixed-radix, Rader
+// and two-step Bluestein kernels that serve many lengths; in registry order.
+using KernelList = std::vector<const KernelInfo*>;
+const KernelList& kernels_of(int64_t n);
+const KernelList& kernels_compiled_for(int64_t n);
+const KernelList& kernels_for_many();
 // The move-only form (mode 1: radix stages removed; mode 2: a plain copy of
 // the array) of an FP32 pass kernel, or null if none is compiled.
 const KernelInfo* find_move_only_kernel(const KernelInfo* k, int mode);

@@ -142,12 +142,12 @@ const KernelInfo* pick_kernel(int n, int64_t pencils, int lmode, int smode, int6
   }
   // any available tile for this length
   const int nt = order[nchoice - 1].nt;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.n == n && k.lmode == lmode && k.smode == smode && k.post_twiddle == tw &&
-        k.persistent == 0 && k.nontemporal == nt && k.precision == 0 && k.plane_rows == 0 &&
-        k.fused_axes == 0 && k.bluestein == 0 && k.mixed == 0 && k.rader == 0 &&
-        k.halves == 0 && k.two_step == 0 && k.move_only == 0)
-      return &k;
+  for (const KernelInfo* k : kernels_of(n))
+    if (k->n == n && k->lmode == lmode && k->smode == smode && k->post_twiddle == tw &&
+        k->persistent == 0 && k->nontemporal == nt && k->precision == 0 && k->plane_rows == 0 &&
+        k->fused_axes == 0 && k->bluestein == 0 && k->mixed == 0 && k->rader == 0 &&
+        k->halves == 0 && k->two_step == 0 && k->move_only == 0)
+      return k;
   return nullptr;
 }
 

@@ -1,5 +1,6 @@
 // Registry of the compiled pass kernels.
 #include <algorithm>
+#include <unordered_map>
 
 #include "../../include/dft3d.h"
 #include "internal.h"
@@ -91,15 +92,50 @@ const std::vector<KernelInfo>& kernel_registry() {
   return table;
 }
 
+namespace {
+
+// The registry by what lookups ask for, every list in registry order.  A plan
+// makes some ten lookups; over the whole registry (2400 kernels, most of them
+// compiled for one length each) they took 11 to 27 us of a plan's building.
+struct KernelIndex {
+  std::unordered_map<int64_t, KernelList> of, compiled_for;
+  KernelList many;
+  KernelIndex() {
+    for (const KernelInfo& k : kernel_registry()) {
+      (k.fixed_n ? compiled_for[k.fixed_n] : of[k.n]).push_back(&k);
+      if (!k.fixed_n && (k.mixed || k.rader || (k.bluestein && k.two_step))) many.push_back(&k);
+    }
+  }
+};
+
+const KernelIndex& kernel_index() {
+  static const KernelIndex index;
+  return index;
+}
+
+const KernelList& list_at(const std::unordered_map<int64_t, KernelList>& m, int64_t n) {
+  static const KernelList none;
+  const auto it = m.find(n);
+  return it == m.end() ? none : it->second;
+}
+
+}  // namespace
+
+const KernelList& kernels_of(int64_t n) { return list_at(kernel_index().of, n); }
+const KernelList& kernels_compiled_for(int64_t n) {
+  return list_at(kernel_index().compiled_for, n);
+}
+const KernelList& kernels_for_many() { return kernel_index().many; }
+
 const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_twiddle,
                               int persistent, int nontemporal) {
-  for (const KernelInfo& k : kernel_registry())
-    if (k.n == n && k.tile == tile && k.lmode == lmode && k.smode == smode &&
-        k.post_twiddle == post_twiddle && k.persistent == persistent &&
-        k.nontemporal == nontemporal && k.precision == 0 && k.plane_rows == 0 &&
-        k.fused_axes == 0 && k.bluestein == 0 && k.mixed == 0 && k.rader == 0 &&
-        k.halves == 0 && k.two_step == 0 && k.move_only == 0)
-      return &k;
+  for (const KernelInfo* k : kernels_of(n))
+    if (k->n == n && k->tile == tile && k->lmode == lmode && k->smode == smode &&
+        k->post_twiddle == post_twiddle && k->persistent == persistent &&
+        k->nontemporal == nontemporal && k->precision == 0 && k->plane_rows == 0 &&
+        k->fused_axes == 0 && k->bluestein == 0 && k->mixed == 0 && k->rader == 0 &&
+        k->halves == 0 && k->two_step == 0 && k->move_only == 0)
+      return k;
   return nullptr;
 }
 
@@ -155,20 +191,20 @@ const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, 
   if (n <= 32 && points >= (int64_t(1) << 25)) return nullptr;
   if (n <= 64 && lmode == MODE_COL && points >= (int64_t(1) << 21)) return nullptr;
   if (n >= 256 && pencils <= 16 * 512) tile = 8;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.two_step && !k.mixed && !k.bluestein && !k.rader && !k.move_only && k.n == n &&
-        k.tile == tile && k.lmode == lmode && k.smode == smode)
-      return &k;
+  for (const KernelInfo* k : kernels_of(n))
+    if (k->two_step && !k->mixed && !k->bluestein && !k->rader && !k->move_only && k->n == n &&
+        k->tile == tile && k->lmode == lmode && k->smode == smode)
+      return k;
   return nullptr;
 }
 
 const KernelInfo* find_halves_kernel(int n, int lmode, int smode, int persistent,
                                      int nontemporal, int move_only) {
-  for (const KernelInfo& k : kernel_registry())
-    if (k.halves && k.n == n && k.lmode == lmode && k.smode == smode &&
-        k.persistent == persistent && k.nontemporal == nontemporal &&
-        k.move_only == move_only)
-      return &k;
+  for (const KernelInfo* k : kernels_of(n))
+    if (k->halves && k->n == n && k->lmode == lmode && k->smode == smode &&
+        k->persistent == persistent && k->nontemporal == nontemporal &&
+        k->move_only == move_only)
+      return k;
   return nullptr;
 }
 
@@ -178,14 +214,14 @@ const KernelInfo* find_move_only_kernel(const KernelInfo* k, int mode) {
     return nullptr;
   if (k->halves && mode == 1)
     return find_halves_kernel(k->n, k->lmode, k->smode, k->persistent, k->nontemporal, 1);
-  for (const KernelInfo& c : kernel_registry()) {
-    if (c.move_only != mode || c.halves || (mode == 1 && c.two_step != k->two_step)) continue;
-    if (mode == 2 && c.n == k->n) return &c;
-    if (mode == 1 && c.n == k->n && c.tile == k->tile && c.lmode == k->lmode &&
-        c.smode == k->smode && c.post_twiddle == k->post_twiddle &&
-        c.persistent == k->persistent && c.nontemporal == k->nontemporal &&
-        c.r0 == k->r0 && c.r1 == k->r1 && c.r2 == k->r2)
-      return &c;
+  for (const KernelInfo* c : kernels_of(k->n)) {
+    if (c->move_only != mode || c->halves || (mode == 1 && c->two_step != k->two_step)) continue;
+    if (mode == 2 && c->n == k->n) return c;
+    if (mode == 1 && c->n == k->n && c->tile == k->tile && c->lmode == k->lmode &&
+        c->smode == k->smode && c->post_twiddle == k->post_twiddle &&
+        c->persistent == k->persistent && c->nontemporal == k->nontemporal &&
+        c->r0 == k->r0 && c->r1 == k->r1 && c->r2 == k->r2)
+      return c;
   }
   return nullptr;
 }
@@ -208,15 +244,15 @@ const KernelInfo* find_mixed_kernel(int64_t n, uint64_t code, int tile, int lmod
   const int variant = mixed_variant(code);
   const KernelInfo* best = nullptr;
   if (tile <= 0)  // a kernel compiled for this length, code and modes, if any
-    for (const KernelInfo& k : kernel_registry())
-      if (k.mixed && !k.two_step && k.fixed_n == n && k.fixed_code == code && k.lmode == lmode &&
-          k.smode == smode)
-        return &k;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.mixed == variant && !k.two_step && k.fixed_n == 0 && k.n > n && k.lmode == lmode &&
-        k.smode == smode && mixed_kernel_runs(k.mixed, k.n, code)) {
-      if (tile > 0 && k.tile == tile) return &k;  // the asked-for tile, if any
-      if (!best || k.n < best->n) best = &k;      // else the first, smallest
+    for (const KernelInfo* k : kernels_compiled_for(n))
+      if (k->mixed && !k->two_step && k->fixed_n == n && k->fixed_code == code &&
+          k->lmode == lmode && k->smode == smode)
+        return k;
+  for (const KernelInfo* k : kernels_for_many())
+    if (k->mixed == variant && !k->two_step && k->fixed_n == 0 && k->n > n && k->lmode == lmode &&
+        k->smode == smode && mixed_kernel_runs(k->mixed, k->n, code)) {
+      if (tile > 0 && k->tile == tile) return k;  // the asked-for tile, if any
+      if (!best || k->n < best->n) best = k;      // else the first, smallest
     }
   return best;
 }
@@ -233,10 +269,10 @@ const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, in
   else if (tile == 16 && pencils <= 16 * (int64_t)(misaligned ? two_step_idle_tiles_off_lines(n)
                                                              : two_step_idle_tiles(n)))
     tile = 8;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.two_step && k.mixed && k.fixed_n == n && k.tile == tile && k.lmode == lmode &&
-        k.smode == smode)
-      return &k;
+  for (const KernelInfo* k : kernels_compiled_for(n))
+    if (k->two_step && k->mixed && k->fixed_n == n && k->tile == tile && k->lmode == lmode &&
+        k->smode == smode)
+      return k;
   return nullptr;
 }
 
@@ -322,15 +358,15 @@ const KernelInfo* find_rader_kernel(int64_t n, int tile) {
   const uint64_t code = mixed_radix_code(n - 1);
   if (!code) return nullptr;
   if (tile <= 0)  // a kernel compiled for this prime and code, if any
-    for (const KernelInfo& k : kernel_registry())
-      if (k.rader && k.fixed_n == n && k.fixed_code == code) return &k;
+    for (const KernelInfo* k : kernels_compiled_for(n))
+      if (k->rader && k->fixed_n == n && k->fixed_code == code) return k;
   const int variant = mixed_variant(code);
   const KernelInfo* best = nullptr;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.rader == variant && !k.two_step && k.fixed_n == 0 && k.n >= n + 1 &&
-        mixed_kernel_runs(variant, k.n, code)) {
-      if (tile > 0 && k.tile == tile) return &k;
-      if (!best || k.n < best->n) best = &k;
+  for (const KernelInfo* k : kernels_for_many())
+    if (k->rader == variant && !k->two_step && k->fixed_n == 0 && k->n >= n + 1 &&
+        mixed_kernel_runs(variant, k->n, code)) {
+      if (tile > 0 && k->tile == tile) return k;
+      if (!best || k->n < best->n) best = k;
     }
   return best;
 }
@@ -343,37 +379,37 @@ bool rader_length(int64_t n, bool any_kernel) {
 
 const KernelInfo* find_bluestein_kernel(int m, int tile) {
   const KernelInfo* first = nullptr;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.bluestein && !k.two_step && k.n == m) {
-      if (k.tile == tile) return &k;
-      if (!first) first = &k;
+  for (const KernelInfo* k : kernels_of(m))
+    if (k->bluestein && !k->two_step && k->n == m) {
+      if (k->tile == tile) return k;
+      if (!first) first = k;
     }
   return first;
 }
 
 const KernelInfo* find_bluestein_two_step_kernel(int64_t n, int lmode, int smode) {
   const KernelInfo* best = nullptr;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.bluestein && k.two_step && k.n >= 2 * n && k.lmode == lmode && k.smode == smode &&
-        (!best || k.n < best->n))
-      best = &k;
+  for (const KernelInfo* k : kernels_for_many())
+    if (k->bluestein && k->two_step && k->n >= 2 * n && k->lmode == lmode && k->smode == smode &&
+        (!best || k->n < best->n))
+      best = k;
   return best;
 }
 
 const KernelInfo* find_fused_axes_kernel(int a, int contig, int persistent, int kind) {
   const int mode = contig ? MODE_ROW : MODE_COL;
   const KernelInfo* other = nullptr;
-  for (const KernelInfo& k : kernel_registry())
-    if (k.fused_axes == kind && k.n == a && k.lmode == mode) {
-      if (k.persistent == persistent) return &k;
-      other = &k;
+  for (const KernelInfo* k : kernels_of(a))
+    if (k->fused_axes == kind && k->n == a && k->lmode == mode) {
+      if (k->persistent == persistent) return k;
+      other = k;
     }
   return other;
 }
 
 const KernelInfo* find_plane_kernel(int n1, int n2) {
-  for (const KernelInfo& k : kernel_registry())
-    if (k.plane_rows == n1 && k.n == n2) return &k;
+  for (const KernelInfo* k : kernels_of(n2))
+    if (k->plane_rows == n1 && k->n == n2) return k;
   return nullptr;
 }
 
@@ -431,24 +467,24 @@ const KernelInfo* find_mfma_kernel(int n, int64_t pencils, int lmode, int smode,
   // persistent form, a tile or a leaf is asked for
   if (tile <= 0 && !persistent && leaf == 0)
     if (const int te = mfma_tile_points(n, pencils * n, lmode == smode))
-      for (const KernelInfo& k : kernel_registry())
-        if (k.mfma_wide < 0 && k.n == n && k.tile == te / n && k.lmode == lmode &&
-            k.smode == smode && k.precision == precision)
-          return &k;
+      for (const KernelInfo* k : kernels_of(n))
+        if (k->mfma_wide < 0 && k->n == n && k->tile == te / n && k->lmode == lmode &&
+            k->smode == smode && k->precision == precision)
+          return k;
   if (leaf == 0) leaf = default_mfma_leaf(n, precision);
   // the wide one-tile form where compiled (length 2048 rotated on write),
   // unless the persistent form or another tile is asked for
   if (tile > 0 || !persistent)
-    for (const KernelInfo& k : kernel_registry())
-      if (k.mfma_wide > 0 && k.n == n && k.lmode == lmode && k.smode == smode &&
-          k.precision == precision && k.mfma_leaf == leaf && (tile <= 0 || k.tile == tile))
-        return &k;
+    for (const KernelInfo* k : kernels_of(n))
+      if (k->mfma_wide > 0 && k->n == n && k->lmode == lmode && k->smode == smode &&
+          k->precision == precision && k->mfma_leaf == leaf && (tile <= 0 || k->tile == tile))
+        return k;
   const KernelInfo* other = nullptr;
-  for (const KernelInfo& k : kernel_registry())
-    if (!k.mfma_wide && k.n == n && k.lmode == lmode && k.smode == smode &&
-        k.precision == precision && k.mfma_leaf == leaf) {
-      if (k.persistent == persistent) return &k;
-      other = &k;
+  for (const KernelInfo* k : kernels_of(n))
+    if (!k->mfma_wide && k->n == n && k->lmode == lmode && k->smode == smode &&
+        k->precision == precision && k->mfma_leaf == leaf) {
+      if (k->persistent == persistent) return k;
+      other = k;
     }
   return other;
 }
