@@ -34,8 +34,11 @@ constexpr int kBatchThreads = 256;
 constexpr int kBatchMaxN = 256;
 
 // In the level form (ONE = 0) contiguous axes from length 16 up run in the two
-// register steps of a plan's own passes (a butterfly of step 1 a thread), so
-// that a problem of a batch keeps the bits of its own plan; strided axes,
+// register steps of a plan's own passes (a butterfly of step 1 a thread, two
+// at 128, whose rotated rows would else be one line long: the 96 pencil
+// problems in tiles of 16 / 32 pencils 404 / 384 us, in the pass kernel's
+// stages 407; 27 of {16, 128, 256}^3 476 / 474, 472), so that contiguous items
+// keep the bits of the problem's own plan; strided axes,
 // whose row segments are the tile, and shorter lengths run the pass kernel's
 // stages in its larger tiles (96 problems of {32, 64, 128}^3, two steps
 // everywhere: 286 against 280 us).  The one-launch form (ONE = 1) runs the
@@ -48,7 +51,7 @@ template <int N, int LM, int ONE> constexpr bool batch_two_step() {
 }
 template <int N, int LM, int ONE> constexpr int batch_tile() {
   if constexpr (batch_two_step<N, LM, ONE>())
-    return kBatchThreads / (N / two_step_split(N));
+    return kBatchThreads / (N / two_step_split(N)) * (N == 128 ? 2 : 1);
   else
     return kBatchThreads / (N / Blocking<N>::E);
 }
@@ -108,8 +111,11 @@ __device__ __forceinline__ void batch_tile_run(const BatchItem& it, int64_t tile
   const int tid = threadIdx.x;
   if constexpr (batch_two_step<N, LM, ONE>()) {
     constexpr int A = two_step_split(N), B = N / A;
-    static_assert(T * B == kBatchThreads && A <= B, "a butterfly of step 1 a thread");
-    two_step_first<A, B, T, LM, kRoots>(it.src, it.a, tile, lds, tid);
+    static_assert(T * B % kBatchThreads == 0 && T * A <= kBatchThreads,
+                  "whole rounds of step 1, one of step 2");
+#pragma unroll
+    for (int i = 0; i < T * B; i += kBatchThreads)
+      two_step_first<A, B, T, LM, kRoots>(it.src, it.a, tile, lds, tid + i);
     two_step_second<A, B, T, SM, kRoots>(it.dst, it.tw, it.a, tile, lds, tid);
   } else {
     using BL = Blocking<N>;

@@ -33,3 +33,8 @@ def test_one_launch_tiles(name, schedule):
 def test_one_launch_tickets_of_the_96_problems():
     assert tiles(SETS["96 problems"], "pencil", "persistent")[0] <= 30644
     assert tiles(SETS["96 problems"], "auto", "persistent")[0] <= 27580
+
+
+def test_level_form_rotates_128_points_in_rows_of_two_lines():
+    assert tiles(SETS["96 problems"], "pencil", "levels")[1][128] == {32}
+    assert tiles(SETS["all lengths"], "pencil", "levels")[1][256] == {16}
