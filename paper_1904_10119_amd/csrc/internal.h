@@ -189,19 +189,30 @@ constexpr int two_step_wide_tile(int64_t n, int64_t pencils) {
   const int64_t b = n / two_step_split(n);
   return b <= 12 || (b <= 16 && pencils >= 4 * kTwoStepWidePencils) ? 64 : 32;
 }
-// Tiles of 32 pencils of the rotating passes of 128 points and more whose rows
-// (as long as there are pencils) do not start on 128-byte lines, from 2^16
-// pencils up: a tile of 16 then writes two half lines a row, which two or more
-// workgroups a CU leave half-written in the L2.  Measured, staged pass / 16 /
-// 32 pencils, us: 192 of 701 x 192 x 703 273 / 350 / 272, 300 of 411 x 300 x 409 (at
-// 168099 pencils) 1 / 1.17 / 1.01 of the staged time, 384 1 / 1.24 / 0.99, 500 1 /
-// 1.19 / 0.90, 600 1 / 1.35 / 1.04; at 60501 pencils 384 1.07 / 1.10, 500 1.04 /
-// 1.01, 600 1.14 / 1.01, 375 0.76 / 0.83, and below that 16 are ahead.
+// Tiles of the rotating passes of 128 points and more whose rows (as long as
+// there are pencils) do not start on 128-byte lines, from 2^16 pencils up: a
+// tile of 16 then writes two half lines a row, which two or more workgroups a
+// CU leave half-written in the L2.  32 pencils, and 48 from 2^18 pencils up,
+// where they fit.  Measured in units of the staged pass in 16 pencils (one
+// workgroup a CU), 16 / 32 / 48 pencils:
+//   168099 pencils: 192 points 1.20 / 1.09 / 1.02, 224 1.20 / 1.04 / 1.15, 240
+//     1.14 / 1.01 / 1.11, 300 1.14 / 1.07 / 1.08, 384 1.24 / 0.99, 500 1.19 / 0.90;
+//   310999: 192 1.21 / 1.13 / 1.05, 224 1.23 / 1.09 / 1.12, 300 1.13 / 1.13 / 1.00,
+//     320 1.04 / 1.20 / 1.05, 336 1.11 / 1.12 / 0.99, 400 0.94 / 0.94 / 0.81;
+//   999999: 168 1.23 / 1.07 / 0.99, 192 1.06 / 0.82 / 0.86, 300 0.88 / 1.06 / 0.82,
+//     336 1.06 / 0.85 / 0.77;
+// 64 pencils are no faster than 48 (300 at 310999 1.12, 192 1.10).  At 60501
+// pencils 384 1.07 / 1.10, 500 1.04 / 1.01, 600 1.14 / 1.01, 375 0.76 / 0.83 in 16 /
+// 32, and below that 16 are ahead.
 constexpr int64_t kTwoStepMisalignedPencils = int64_t(1) << 16;
-constexpr int two_step_misaligned_tile(int64_t n) {
-  if (n < 128 || !two_step_split(n) || two_step_tile(n) != 16) return 0;
+constexpr int two_step_misaligned_tile(int64_t n, int64_t pencils) {
+  if (n < 128 || pencils < kTwoStepMisalignedPencils || !two_step_split(n) ||
+      two_step_tile(n) != 16)
+    return 0;
   const int64_t a = two_step_split(n), b = n / a;
-  return 32 * b <= 1024 && 32 * ((a * (b | 1)) | 1) * 8 <= 160 * 1024 ? 32 : 0;
+  for (int t = pencils >= 4 * kTwoStepMisalignedPencils ? 48 : 32; t > 16; t -= 16)
+    if (t * b <= 1024 && t * ((a * (b | 1)) | 1) * 8 <= 160 * 1024) return t;
+  return 0;
 }
 // The two-step kernel for length n, a number of pencils, the load and store
 // modes and the stride between output points k, or null.

@@ -264,8 +264,8 @@ const KernelInfo* find_two_step_kernel(int64_t n, int64_t pencils, int lmode, in
   const bool misaligned = rows_off_lines(pencils, lmode, smode, oks);
   if (const int wide = two_step_wide_tile(n, pencils))
     tile = wide;
-  else if (misaligned && pencils >= kTwoStepMisalignedPencils && two_step_misaligned_tile(n))
-    tile = two_step_misaligned_tile(n);
+  else if (misaligned && two_step_misaligned_tile(n, pencils))
+    tile = two_step_misaligned_tile(n, pencils);
   else if (tile == 16 && pencils <= 16 * (int64_t)(misaligned ? two_step_idle_tiles_off_lines(n)
                                                              : two_step_idle_tiles(n)))
     tile = 8;

@@ -156,7 +156,7 @@ fft_two_step_kernel(const PassLaunch la) {
 }
 
 // Threads of a two-step workgroup: a butterfly of step 1 for each (at most
-// 16 x 64).
+// 16 x 64 = 1024).
 constexpr int two_step_threads(int b, int t) { return (t * b + 63) / 64 * 64; }
 
 template <int A, int B, int T, int LM, int SM, int FORM>
@@ -230,8 +230,10 @@ void add_two_step_kernels(std::vector<KernelInfo>& v) {
     constexpr int W1 = two_step_wide_tile(LO, int64_t(1) << 40);
     if constexpr (W0 > 0) add_two_step_modes<A, B, W0>(v);
     if constexpr (W1 != W0) add_two_step_modes<A, B, W1>(v);
-    if constexpr (constexpr int M = two_step_misaligned_tile(LO); M > 0)
-      v.push_back(kernel_info_two_step<A, B, M, MODE_ROW, MODE_COL>());
+    constexpr int M0 = two_step_misaligned_tile(LO, kTwoStepMisalignedPencils);
+    constexpr int M1 = two_step_misaligned_tile(LO, int64_t(1) << 40);
+    if constexpr (M0 > 0) v.push_back(kernel_info_two_step<A, B, M0, MODE_ROW, MODE_COL>());
+    if constexpr (M1 != M0) v.push_back(kernel_info_two_step<A, B, M1, MODE_ROW, MODE_COL>());
   }
 }
 

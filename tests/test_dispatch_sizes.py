@@ -140,16 +140,19 @@ def check_sampled(shape, schedule, seed):
 
 
 @pytest.mark.parametrize("n", [130, 144, 192, 240, 300, 375, 384, 500, 600, 625])
-def test_misaligned_rotation_takes_tiles_of_32(n):
+def test_misaligned_rotation_takes_wider_tiles(n):
     """From 2^16 pencils up the rotating passes whose rows do not start on
-    128-byte lines take 32 pencils; aligned rows, fewer pencils and the orders
-    that keep the layout take 16 (or 8 on small grids)."""
+    128-byte lines take 32 pencils, from 2^18 48 where they fit; aligned rows,
+    fewer pencils and the orders that keep the layout take 16."""
     def tile(shape, schedule="pencil", at=0):
         p = passes(shape, schedule, fused_plane=0)[at]
         assert p["mixed"] and p["lds_bytes"] <= 160 * 1024
         return p["tile"]
     assert tile((257, 257, n)) == 32 and tile((256, 256, n)) == 16
     assert tile((257, 253, n)) == 16
+    a, b = passes((1, 1, n))[0]["split"]
+    fits = 48 * b <= 1024 and 48 * (a * (b | 1) | 1) * 8 <= 160 * 1024
+    assert tile((513, 513, n)) == (48 if fits else 32) and tile((512, 528, n)) == 16
     assert tile((257, 257, n), "slab") == 16 and tile((n, 257, 257), "slab", -1) == 16
 
 
@@ -168,10 +171,10 @@ def test_wide_tiles_on_the_gpu(shape, schedule):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", [(257, 257, 130), (257, 192, 259), (375, 259, 257),
-                                   (257, 257, 625)])
+                                   (257, 257, 625), (515, 130, 513), (300, 513, 513)])
 def test_misaligned_tiles_of_32_on_the_gpu(shape):
     """Tiles of 32 pencils with rows off the 128-byte lines and a ragged last
     tile."""
     print("case misaligned tiles", shape, flush=True)
-    assert any(p["tile"] == 32 and p["split"] for p in passes(shape))
+    assert any(p["tile"] in (32, 48) and p["split"] for p in passes(shape))
     check_sampled(shape, "pencil", 82)

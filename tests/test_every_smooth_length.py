@@ -30,7 +30,7 @@ LENGTHS = [n for n in range(6, 2001) if split(n)]
 def cases(n):
     """(shape, schedule, the pass of length n, its tile): small ragged grids,
     grids past the idle-CU rule, the wide tiles below 128 points and the tiles
-    of 32 for rows off the 128-byte lines."""
+    of 32 and 48 for rows off the 128-byte lines."""
     b = split(n)[1]
     base = 16 if b <= 40 and 16 * (n // b * (b | 1) | 1) * 8 <= 160 * 1024 else 8
     small = base if n < 360 else 8
@@ -46,8 +46,13 @@ def cases(n):
         for k, t in wide:
             out += [(k + (n,), "pencil", 0, t), (k + (n,), "slab", 0, t),
                     ((n,) + k, "slab", -1, t)]
-    if n >= 128 and base == 16 and b <= 32 and 32 * (n // b * (b | 1) | 1) * 8 <= 160 * 1024:
-        out.append(((255, 273, n), "pencil", 0, 32))
+    if n >= 128 and base == 16:
+        fits = [t for t in (32, 48) if t * b <= 1024 and
+                t * (n // b * (b | 1) | 1) * 8 <= 160 * 1024]
+        if fits:
+            out.append(((255, 273, n), "pencil", 0, 32))
+        if fits[1:]:
+            out.append(((525, 507, n), "pencil", 0, 48))
     return out
 
 
