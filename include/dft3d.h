@@ -26,7 +26,8 @@
  *               steps (those above 700 in tiles of 16 pencils) and the pencil
  *               rows of an axis of at most 640 would not start on 128-byte
  *               lines (the product of the other two axes is no multiple of
- *               16), unless an option names a tile, radices or a pencil form.
+ *               16; from 2^25 points two such axes, or one and none above
+ *               640), unless an option names a tile, radices or a pencil form.
  *
  * Data: complex64 = two IEEE binary32 (re, im), interleaved, 8 bytes per
  * point; C order (n0, n1, n2), n2 contiguous; device pointers, 16-byte

@@ -771,10 +771,12 @@ void pencil_cycled_other(Builder& b, const int64_t n[3]) {
 // with two or more workgroups a CU (lengths up to 640) they leave the L2
 // half-written.  Measured against the rotation in tiles of 16, rotation / slab:
 // 375 x 486 x 400 737 / 673 us, 375^3 659 / 538, 455 x 325 x 195 339 / 270, 105^3
-// 22.5 / 20.9.  With the rotation's tiles of 32 for such rows
+// 22.5 / 20.9.  With the rotation's wider tiles for such rows
 // (two_step_misaligned_tile) the two are level on the whole, 0.99 in the mean
 // over 84 shapes (375 x 486 x 400 692 / 672, 455 x 325 x 195 315 / 270, 441^3 858 /
-// 925, 243^3 132 / 146), and the slab needs no workspace.  Longer misaligned
+// 925, 243^3 132 / 146), and the slab needs no workspace; with one such axis
+// beside a longer one from 2^25 points up the rotation is ahead (0.97 in the
+// mean over nine, 400 x 875 x 300 1004 / 1057).  Longer misaligned
 // passes 675^3 3.06 / 3.24 ms; aligned ones 324^3 326 / 341 us, 600 x 600 x 18 64 /
 // 72; long axes in tiles of 8 pencils, whose strided passes move 64-byte
 // segments, 882 x 882 x 64 509 / 567, 1029 x 1029 x 64 713 / 766 (686 x 686 x 64
@@ -784,12 +786,15 @@ bool slab_suits_other(const int64_t n[3], const Options& opt) {
   if (total < (int64_t(1) << 20) || total * 8 >= kCycleBytes || opt.tile > 0 || opt.radices ||
       opt.pencil_order >= 0 || opt.pencil_group)
     return false;
-  bool misaligned = false;
+  int misaligned = 0;
+  bool longer = false;
   for (int d = 0; d < 3; ++d) {
     if (!two_step_split(n[d]) || (n[d] > 700 && two_step_tile(n[d]) < 16)) return false;
-    misaligned = misaligned || (n[d] <= 640 && total / n[d] % 16 != 0);
+    misaligned += n[d] <= 640 && total / n[d] % 16 != 0;
+    longer = longer || n[d] > 640;
   }
-  return misaligned;
+  return misaligned > 1 ||
+         (misaligned == 1 && !(longer && total >= (int64_t(1) << 25)));
 }
 
 // Grouped pencil schedule: planes of axis 0 taken G at a time through the

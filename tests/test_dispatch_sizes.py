@@ -85,6 +85,17 @@ def test_misaligned_rotation_of_powers_of_two():
     assert passes((251, 251, 64), "slab")[0]["split"] == [8, 8]
 
 
+def test_auto_with_one_misaligned_axis_beside_a_longer_one():
+    """From 2^25 points up such shapes keep the rotation, whose wide tiles are
+    ahead of the slab there; two misaligned axes or no longer one take the slab."""
+    def sched(shape):
+        return dft3d.describe(shape, "auto")["schedule"]
+    assert sched((400, 875, 300)) == "pencil" and sched((400, 945, 300)) == "pencil"
+    assert sched((400, 539, 300)) == "slab" and sched((275, 750, 504)) == "pencil"
+    assert sched((56, 700, 275)) == "slab" and sched((308, 169, 630)) == "slab"
+    assert sched((468, 392, 735)) == "slab"
+
+
 SHORT = [48, 49, 56, 60, 72, 80, 90, 96, 98, 100, 104, 105, 112, 117, 120, 125, 126]
 
 
