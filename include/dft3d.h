@@ -27,7 +27,8 @@
  *               rows of an axis of at most 640 would not start on 128-byte
  *               lines (the product of the other two axes is no multiple of
  *               16; from 2^25 points two such axes, or one and none above
- *               640), unless an option names a tile, radices or a pencil form.
+ *               640 or n2 a multiple of 8), unless an option names a tile,
+ *               radices or a pencil form.
  *
  * Data: complex64 = two IEEE binary32 (re, im), interleaved, 8 bytes per
  * point; C order (n0, n1, n2), n2 contiguous; device pointers, 16-byte

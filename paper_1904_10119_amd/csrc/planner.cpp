@@ -775,8 +775,10 @@ void pencil_cycled_other(Builder& b, const int64_t n[3]) {
 // (two_step_misaligned_tile) the two are level on the whole, 0.99 in the mean
 // over 84 shapes (375 x 486 x 400 692 / 672, 455 x 325 x 195 315 / 270, 441^3 858 /
 // 925, 243^3 132 / 146), and the slab needs no workspace; with one such axis
-// beside a longer one from 2^25 points up the rotation is ahead (0.97 in the
-// mean over nine, 400 x 875 x 300 1004 / 1057).  Longer misaligned
+// beside a longer one from 2^25 points up it is the slab's own column segments
+// that decide: on 64-byte halves of the lines (n2 a multiple of 8) the slab is
+// ahead (0.93 .. 1.005 over 14 shapes, 1053 x 210 x 936 2.00 / 2.09 ms), off
+// them the rotation (0.90 .. 1.005 over 36, 400 x 875 x 300 1004 / 1057 us).  Longer misaligned
 // passes 675^3 3.06 / 3.24 ms; aligned ones 324^3 326 / 341 us, 600 x 600 x 18 64 /
 // 72; long axes in tiles of 8 pencils, whose strided passes move 64-byte
 // segments, 882 x 882 x 64 509 / 567, 1029 x 1029 x 64 713 / 766 (686 x 686 x 64
@@ -794,7 +796,7 @@ bool slab_suits_other(const int64_t n[3], const Options& opt) {
     longer = longer || n[d] > 640;
   }
   return misaligned > 1 ||
-         (misaligned == 1 && !(longer && total >= (int64_t(1) << 25)));
+         (misaligned == 1 && (n[2] % 8 == 0 || !longer || total < (int64_t(1) << 25)));
 }
 
 // Grouped pencil schedule: planes of axis 0 taken G at a time through the

@@ -162,10 +162,13 @@ const KernelInfo* find_kernel(int n, int tile, int lmode, int smode, int post_tw
 //    lines, the pass kernel's 64 and 32 pencils (251 x 64 x 251 11.7 against 12.7,
 //    255 x 256 x 511 109 / 124; below 127 x 64 x 129 8.1 / 7.1, 127 x 256 x 129
 //    13.1 / 13.3; 128 and 512 are level or ahead in two steps);
-//  - 512 along strided axes from 2^23 points up, and from 2^23 to 2^24 in every
-//    order but rows, the pass kernel (512 x 64 x 256 depth 25.0 against 27.0,
-//    512 x 512 x 64 columns 45.3 / 48.7, 512 x 256 x 64 rotated 24.9 / 27.3; rows
-//    and the rotation from 2^24 points up are level or 3 % faster in two steps);
+//  - 512 from 2^23 points up along strided axes whose points lie less than 2 KB
+//    or 128 KB and more apart, and from 2^23 to 2^24 in the rotation, the pass
+//    kernel (512 x 64 x 256 depth 25.0 against 27.0, 512 x 512 x 64 columns 45.3
+//    / 48.7, 512 x 256 x 64 rotated 24.9 / 27.3; columns between, rows and the
+//    rotation from 2^24 points up are level or 1 to 3 % faster in two steps:
+//    whole slabs 16 x 512 x 1024 79.9 / 78.5, 8 x 512 x 2048 84.1 / 82.9, 64 x
+//    512 x 256 74.8 / 74.1);
 //  - 16 and 32 from 2^25 points up the pass kernel in every order: the cycled
 //    pencil passes of such arrays read pencils a plane apart and write row
 //    segments of a tile's pencils (16 x 1024 x 2048 102 against 127, 32 x 1024
@@ -186,7 +189,7 @@ const KernelInfo* find_two_step_power_kernel(int n, int64_t pencils, int lmode, 
   if (n == 128 && points >= (int64_t(1) << 23)) return nullptr;
   if (n == 256 && points > (int64_t(1) << 25)) tile = 32;
   if (n == 512 && smode == MODE_COL && points >= (int64_t(1) << 23) &&
-      (lmode == MODE_COL || points < (int64_t(1) << 24)))
+      (lmode == MODE_COL ? oks < 256 || oks >= (1 << 14) : points < (int64_t(1) << 24)))
     return nullptr;
   if (n <= 32 && points >= (int64_t(1) << 25)) return nullptr;
   if (n <= 64 && lmode == MODE_COL && points >= (int64_t(1) << 21)) return nullptr;

@@ -33,15 +33,20 @@ def test_64_points_on_large_grids_take_the_pass_kernel(schedule):
 
 
 def test_512_points_on_middle_grids_take_the_pass_kernel():
-    """Strided axes of 512 from 2^23 points up, and the rotation from 2^23 to
-    2^24, take the pass kernel; rows and the larger rotations two steps."""
+    """From 2^23 points up strided axes of 512 whose points lie less than 2 KB or
+    128 KB and more apart, and from 2^23 to 2^24 the rotation, take the pass
+    kernel; the columns between, rows and the larger rotations two steps."""
     def split(shape, schedule, at):
         p = passes(shape, schedule, fused_plane=0)[at]
         assert p["n"] == 512
         return p["split"]
     assert split((512, 128, 64), "slab", -1) == [16, 32]      # 2^22
     assert split((512, 256, 64), "slab", -1) == []            # 2^23
-    assert split((64, 512, 512), "slab", 1) == []             # 2^24
+    assert split((512, 512, 64), "slab", 1) == []             # 512 B apart
+    assert split((64, 512, 256), "slab", 1) == [16, 32]       # 2 KB
+    assert split((16, 512, 1024), "slab", 1) == [16, 32]
+    assert split((8, 512, 4096), "slab", 1) == [16, 32]       # 32 KB
+    assert split((512, 4, 4096), "slab", -1) == []            # 128 KB
     assert split((64, 512, 512), "slab", 0) == [16, 32]
     assert split((64, 256, 512), "pencil", 0) == []           # 2^23, rotated
     assert split((128, 256, 512), "pencil", 0) == [16, 32]    # 2^24
@@ -87,11 +92,15 @@ def test_misaligned_rotation_of_powers_of_two():
 
 def test_auto_with_one_misaligned_axis_beside_a_longer_one():
     """From 2^25 points up such shapes keep the rotation, whose wide tiles are
-    ahead of the slab there; two misaligned axes or no longer one take the slab."""
+    ahead of the slab where the slab's column segments are off the 64-byte halves
+    of the lines too (n2 no multiple of 8); the others take the slab."""
     def sched(shape):
         return dft3d.describe(shape, "auto")["schedule"]
     assert sched((400, 875, 300)) == "pencil" and sched((400, 945, 300)) == "pencil"
-    assert sched((400, 539, 300)) == "slab" and sched((275, 750, 504)) == "pencil"
+    assert sched((640, 343, 675)) == "pencil" and sched((378, 432, 660)) == "pencil"
+    assert sched((275, 750, 504)) == "slab" and sched((756, 275, 432)) == "slab"
+    assert sched((1053, 210, 936)) == "slab"
+    assert sched((400, 539, 300)) == "slab"
     assert sched((56, 700, 275)) == "slab" and sched((308, 169, 630)) == "slab"
     assert sched((468, 392, 735)) == "slab"
 
